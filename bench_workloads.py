@@ -23,13 +23,12 @@ from paper_2508_16522_amd import workloads as wl
 
 METRIC = "tasks/sec + per-task overhead (ns) + min effective task granularity, 1 GPU"
 ROOT = os.path.dirname(os.path.abspath(__file__))
-# integer-VALU peak of the task body from the unit counts: the published
-# fp32 vector peak (157.3 TFLOP/s = 256 CUs x 2.4 GHz x 128 lanes x 2 flops
-# per fused multiply-add) gives 128 32-bit lanes per clock per CU; the
-# compiled mix is 8 VALU instructions per word-round (3 shifts, 3 xors, one
-# 32-bit multiply, one add), so 256 x 2.4e9 x 128 / 8 word-rounds/s.  (64
-# lanes per clock would give half this, which the measured mix rate exceeds.)
-ALU_PEAK_WORD_ROUNDS = 256 * 2.4e9 * 128 / 8
+# integer-VALU peak of the task body: 256 CUs x 2.4 GHz x 64 lanes per clock
+# (four SIMDs of 16; every instruction of the mix, the 32-bit multiply and the
+# 64-bit shifts included, was measured at four cycles per wavefront), and six
+# instructions per word-round (three shifts, two of them shared by two words,
+# three xors, one of which also adds, and a multiply).
+ALU_PEAK_WORD_ROUNDS = 256 * 2.4e9 * 64 / 6
 
 
 def log(msg):

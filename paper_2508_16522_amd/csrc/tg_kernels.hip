@@ -30,11 +30,9 @@
 //    when it sees the abort flag.  A long critical path that keeps most
 //    workers idle therefore never trips the watchdog while it advances.
 #include "tg_internal.h"
+#include "tg_mix.h"
 
 namespace tg {
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kSC1 = 16;  // buffer cache policy: device-scope coherent access
 
@@ -81,17 +79,6 @@ __device__ __forceinline__ uint64_t sm64(uint64_t z) {
 }
 // low 32 bits of sm64(key ^ idx), key = sm64(seed ^ (stream << 32))
 __device__ __forceinline__ uint32_t h32k(uint64_t key, uint64_t idx) { return (uint32_t)sm64(key ^ idx); }
-
-template <class V>
-__device__ __forceinline__ V mix_rounds(V x, uint32_t R) {
-  for (uint32_t r = 0; r < R; ++r) {
-    x ^= x << 13;
-    x ^= x >> 17;
-    x ^= x << 5;
-    x = x * 0x9E3779B1u + 0x7F4A7C15u;
-  }
-  return x;
-}
 
 // Wrap-around sum over the 64 lanes (all active), returned wave-uniform.
 // Cross-lane moves within each 16-lane row use DPP (swap neighbours, swap
@@ -302,7 +289,7 @@ __device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecPar
         }
       }
     }
-    V x = mix_rounds<V>(acc ^ tid, R);
+    V x = mix_rounds(V(acc ^ tid), R);
     if (valid) {
       buf_store<VEC>(x, wr, k0 * 4);
 #pragma unroll
@@ -367,7 +354,7 @@ __device__ __forceinline__ uint32_t body_implicit(const Team& tm, const ExecPara
     u32x4 x = load4(a, wt, S, len);
     for (uint64_t base = 0; base < len; base += step) {
       const u32x4 y = base + step < len ? load4(a + base + step, wt, S, len - base - step) : u32x4{0, 0, 0, 0};
-      x = mix_rounds<u32x4>(x ^ key, R);
+      x = mix_rounds(u32x4(x ^ key), R);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint64_t o = base + wt + (uint64_t)k * S;

@@ -16,21 +16,17 @@
 //                   signals back with one device atomic.
 #include "taskgraph.h"
 #include "tg_internal.h"
+#include "tg_mix.h"
 
 namespace {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+using tg::u32x4;
 
 // The mix at the executor's occupancy: same launch bounds and waves per SIMD.
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void p_mix(uint32_t* a, uint32_t rounds) {
   const size_t base = ((size_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
   u32x4 x = {a[base], a[base + 1], a[base + 2], a[base + 3]};
-  for (uint32_t r = 0; r < rounds; ++r) {
-    x ^= x << 13;
-    x ^= x >> 17;
-    x ^= x << 5;
-    x = x * 0x9E3779B1u + 0x7F4A7C15u;
-  }
+  x = tg::mix_rounds(x, rounds);
   a[base] = x[0];
   a[base + 1] = x[1];
   a[base + 2] = x[2];
@@ -48,14 +44,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     u32x4 x = {a[base], a[base + 1], a[base + 2], a[base + 3]};
     u32x4 y = {a[base + 4], a[base + 5], a[base + 6], a[base + 7]};
     for (uint32_t r = 0; r < rounds; ++r) {
-      x ^= x << 13;
-      y ^= y << 13;
-      x ^= x >> 17;
-      y ^= y >> 17;
-      x ^= x << 5;
-      y ^= y << 5;
-      x = x * 0x9E3779B1u + 0x7F4A7C15u;
-      y = y * 0x9E3779B1u + 0x7F4A7C15u;
+      uint32_t x0 = x[0], x1 = x[1], x2 = x[2], x3 = x[3], y0 = y[0], y1 = y[1], y2 = y[2], y3 = y[3];
+      tg::mix_pair(x0, x1);
+      tg::mix_pair(x2, x3);
+      tg::mix_pair(y0, y1);
+      tg::mix_pair(y2, y3);
+      x = u32x4{x0, x1, x2, x3};
+      y = u32x4{y0, y1, y2, y3};
     }
     a[base] = x[0];
     a[base + 1] = x[1];
