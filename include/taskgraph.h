@@ -383,9 +383,10 @@ tg_status tg_last_user_dag(uint32_t n, const uint64_t* req_ptr, const tg_region_
  *   stream      : every kernel runs on it; the call returns when the DAG is
  *                 complete (it waits for the stream, which therefore must not
  *                 be capturing).
- * The caller owns every array.  Scratch device memory (the interval table,
- * buckets, counts, scan partials) is allocated with hipMalloc for the call
- * and freed before it returns.  TG_EINVAL for a bad requirement list (the
+ * The caller owns every array.  Scratch device memory (interval lists,
+ * counts, scan partials) comes from a 32 MiB array of device memory in the
+ * library's code object if no other call has it, else (and where it does not
+ * fit) from hipMalloc, freed before the call returns.  TG_EINVAL for a bad requirement list (the
  * message names the fault), TG_EDEVICE for a HIP error. */
 tg_status tg_infer_dag(uint32_t ntasks, const uint64_t* req_ptr, const tg_region_req* reqs, uint64_t nreqs,
                        uint64_t index_space, uint64_t* row_ptr, uint32_t* col, uint64_t col_cap, uint64_t* num_edges,
