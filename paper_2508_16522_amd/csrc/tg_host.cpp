@@ -922,6 +922,7 @@ tg_status plan_layout(const std::vector<tg_graph>& gs, uint64_t nw_req, uint32_t
         r.tid = v;
         r.graph = gi;
         r.rounds = g->rounds[v];
+        r.shape = tg::task_shape(g->mode, g->n);
         const uint64_t d0 = g->dpred_ptr[v], d1 = g->dpred_ptr[v + 1];
         r.npred = (uint32_t)(d1 - d0);
         if (expl) {

@@ -35,31 +35,36 @@ constexpr uint32_t kInSucc = 8;  // successor positions held in the record
 // positions are inline, so a task's payload loads depend on one load (the
 // record) and its edge signals on none after the payload store.
 struct alignas(128) TaskRec {
-  uint64_t out;            // dw 0-1  explicit: device address of this task's payload
+  uint32_t succ[kInSucc];  // dw 0-7  first successor positions (lane i of the wavefront that
+                           //         loaded the record signals succ[i]: no cross-lane move)
+  uint64_t out;            // dw 8-9  explicit: device address of this task's payload
                            //         implicit: device address of its first region requirement
-  uint32_t tid;            // dw 2    task id inside its graph (creation index)
-  uint32_t graph;          // dw 3    index into the graph table
-  uint32_t pred_beg;       // dw 4    explicit: all predecessors at pred_addr[pred_beg ..]
-  uint32_t npred;          // dw 5    number of distinct predecessors (= in-degree)
-  uint32_t succ_beg;       // dw 6    all successors at succ_pos[succ_beg ..]
-  uint32_t nsucc;          // dw 7    number of successors
-  uint32_t rounds;         // dw 8    mix rounds
-  uint32_t nreq;           // dw 9    implicit: number of region requirements
-  uint64_t pred[kInPred];  // dw 10-21 first predecessors' payload addresses
-  uint32_t succ[kInSucc];  // dw 22-29 first successor positions
-  uint32_t pad[2];         // dw 30-31
+  uint32_t tid;            // dw 10   task id inside its graph (creation index)
+  uint32_t graph;          // dw 11   index into the graph table
+  uint32_t pred_beg;       // dw 12   explicit: all predecessors at pred_addr[pred_beg ..]
+  uint32_t npred;          // dw 13   number of distinct predecessors (= in-degree)
+  uint32_t succ_beg;       // dw 14   all successors at succ_pos[succ_beg ..]
+  uint32_t nsucc;          // dw 15   number of successors
+  uint32_t rounds;         // dw 16   mix rounds
+  uint32_t nreq;           // dw 17   implicit: number of region requirements
+  uint64_t pred[kInPred];  // dw 18-29 first predecessors' payload addresses
+  uint32_t shape;          // dw 30   task_shape(mode, payload words): the loads need no graph entry
+  uint32_t pad;            // dw 31
 };
 static_assert(sizeof(TaskRec) == 128, "task record is 32 dwords");
 enum : uint32_t {
-  kDwOut = 0, kDwTid = 2, kDwGraph = 3, kDwPredBeg = 4, kDwNpred = 5, kDwSuccBeg = 6, kDwNsucc = 7,
-  kDwRounds = 8, kDwNreq = 9, kDwPred = 10, kDwSucc = 22
+  kDwSucc = 0, kDwOut = 8, kDwTid = 10, kDwGraph = 11, kDwPredBeg = 12, kDwNpred = 13, kDwSuccBeg = 14,
+  kDwNsucc = 15, kDwRounds = 16, kDwNreq = 17, kDwPred = 18, kDwShape = 30
 };
 static_assert(offsetof(TaskRec, tid) == 4 * kDwTid && offsetof(TaskRec, graph) == 4 * kDwGraph &&
                   offsetof(TaskRec, pred_beg) == 4 * kDwPredBeg && offsetof(TaskRec, npred) == 4 * kDwNpred &&
                   offsetof(TaskRec, succ_beg) == 4 * kDwSuccBeg && offsetof(TaskRec, nsucc) == 4 * kDwNsucc &&
                   offsetof(TaskRec, rounds) == 4 * kDwRounds && offsetof(TaskRec, nreq) == 4 * kDwNreq &&
-                  offsetof(TaskRec, pred) == 4 * kDwPred && offsetof(TaskRec, succ) == 4 * kDwSucc,
+                  offsetof(TaskRec, pred) == 4 * kDwPred && offsetof(TaskRec, succ) == 4 * kDwSucc &&
+                  offsetof(TaskRec, out) == 4 * kDwOut && offsetof(TaskRec, shape) == 4 * kDwShape,
               "record dword map");
+// Mode (1 explicit, 2 implicit) and payload words (at most 65,536) of a task.
+__host__ __device__ inline uint32_t task_shape(uint32_t mode, uint32_t n) { return mode << 24 | n; }
 
 // Region requirement on the device (implicit mode).
 struct alignas(16) ReqDev {

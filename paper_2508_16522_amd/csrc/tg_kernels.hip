@@ -18,6 +18,11 @@
 //    so there is no contended queue head or tail (a single-address device
 //    atomic costs about 11 ns on this part; distinct addresses sustain
 //    about 27 G atomics/s).
+//    Polling, taking and signalling run in scalar registers, and every
+//    memory round trip of a task has other work behind it (k_exec_wave).  A
+//    stencil of 1024 x 500 tasks with 256-word payloads and no mix rounds
+//    takes 1.9 us a level; with vector-register state, returning edge atomics
+//    and the digest before the signals it took 2.75 us.
 //  * Publication: payload and array writes use device-coherent (sc1)
 //    stores; before the first out-edge decrement the worker waits for all
 //    its stores to complete (s_waitcnt vmcnt(0)).  Readers load with sc1.
@@ -42,8 +47,14 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 
 // Wait until every outstanding vector memory operation of this wave has
 // completed; the memory clobber keeps the compiler from moving memory
-// operations across it.
-__device__ __forceinline__ void vm_drain() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+// operations across it.  The builtin says the same (vmcnt 0, the other
+// counters unlimited) to the pass that inserts waits, which does not look
+// into the asm: loads issued before the drain need no wait after it.
+__device__ __forceinline__ void vm_drain() {
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  asm volatile("" ::: "memory");
+}
 
 // Read-only tables (records, graph table, predecessor addresses, requirement
 // lists) are read through the constant address space so that wave-uniform
@@ -149,14 +160,14 @@ __device__ __forceinline__ uint32_t rl(uint32_t v, uint32_t k) { return __builti
 // A task record as one team holds it: every wavefront loads the 128-byte
 // record with one coalesced load (lane i: dword i % 32) and reads the scalar
 // fields out with readlane.  succ0 is the successor this team index signals
-// first (index t), fetched together with the record so that no load stands
-// between the payload store and the edge signals.
+// first (index t): the record's first dwords, so lanes 0-7 hold theirs already,
+// and no load stands between the payload store and the edge signals.
 struct Rec {
   uint32_t v;
   uint64_t out;
-  uint32_t tid, graph, pred_beg, npred, succ_beg, nsucc, rounds, nreq;
+  uint32_t tid, graph, npred, succ_beg, nsucc, rounds, shape;
   uint32_t succ0;
-  uint32_t* digest;  // the graph's digest array
+  uint32_t* digest;  // the graph's digests
 };
 
 // This lane's dword of the record at `pos`.  Records are read-only while a
@@ -167,27 +178,24 @@ __device__ __forceinline__ uint32_t rec_dword(const ExecParams& P, uint32_t pos,
 
 template <class Team>
 __device__ __forceinline__ void unpack_rec(const Team& tm, const ExecParams& P, uint32_t v, Rec& r) {
-  const uint32_t lane = tm.t & 63u;
   r.v = v;
   r.out = (uint64_t)rl(r.v, kDwOut) | ((uint64_t)rl(r.v, kDwOut + 1) << 32);
   r.tid = rl(r.v, kDwTid);
   r.graph = rl(r.v, kDwGraph);
-  r.pred_beg = rl(r.v, kDwPredBeg);
   r.npred = rl(r.v, kDwNpred);
   r.succ_beg = rl(r.v, kDwSuccBeg);
   r.nsucc = rl(r.v, kDwNsucc);
   r.rounds = rl(r.v, kDwRounds);
-  r.nreq = rl(r.v, kDwNreq);
-  const uint32_t inl = __shfl(r.v, (int)(kDwSucc + (lane & (kInSucc - 1))), 64);
-  const uint32_t j = tm.t;
-  r.succ0 = 0;
-  if (j < r.nsucc) r.succ0 = j < kInSucc ? inl : P.succ_pos[r.succ_beg + j];
+  r.shape = rl(r.v, kDwShape);
+  r.digest = as_const(P.gtab)[r.graph].digest;
+  r.succ0 = r.v;
+  if (r.nsucc > kInSucc && tm.t >= kInSucc && tm.t < r.nsucc) r.succ0 = P.succ_pos[r.succ_beg + tm.t];
 }
 
 // Payload address of predecessor j (j wave-uniform).
 __device__ __forceinline__ uint64_t pred_at(const ExecParams& P, const Rec& r, uint32_t j) {
   if (j < kInPred) return (uint64_t)rl(r.v, kDwPred + 2 * j) | ((uint64_t)rl(r.v, kDwPred + 2 * j + 1) << 32);
-  return as_const(P.pred_addr)[r.pred_beg + j];
+  return as_const(P.pred_addr)[rl(r.v, kDwPredBeg) + j];
 }
 
 // ------------------------------------------------------------------ bodies
@@ -220,78 +228,123 @@ __device__ __forceinline__ uint32_t elem(typename VecT<VEC>::T v, int i) {
   else return v[i];
 }
 
+// Called by a body once its first loads are issued: the list executors fetch
+// the record of the next task there, behind loads the body waits for anyway.
+struct NoPrefetch {
+  __device__ __forceinline__ void operator()() const {}
+};
+
+// The input of one chunk (words k0 .. k0 + VEC - 1 of every lane) of a task of
+// at most five predecessors: all loads issued together, one memory round trip.
+template <int VEC, class Prefetch>
+__device__ __forceinline__ typename VecT<VEC>::T gather5(const ExecParams& P, const Rec& r, uint32_t nbytes,
+                                                         uint32_t k0, Prefetch&& prefetch) {
+  typedef typename VecT<VEC>::T V;
+  auto in = [&](uint32_t j) { return buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j), nbytes), k0 * 4u); };
+  const V p0 = in(0);
+  if (r.npred == 1) {
+    prefetch();
+    return p0;
+  }
+  const V p1 = in(1);
+  if (r.npred == 2) {
+    prefetch();
+    return p0 + p1;
+  }
+  const V p2 = in(2);
+  if (r.npred == 3) {
+    prefetch();
+    return p0 + p1 + p2;
+  }
+  const V p3 = in(3);
+  if (r.npred == 4) {
+    prefetch();
+    return (p0 + p1) + (p2 + p3);
+  }
+  const V p4 = in(4);
+  prefetch();
+  return ((p0 + p1) + (p2 + p3)) + p4;
+}
+
 // Explicit body over words k = k0, k0 + VEC*S, ... handled VEC at a time.
 // The chunk loop and the mix-round loop have wave-uniform trip counts (n,
-// the team size and R are uniform), so both run under scalar loop control;
-// lanes whose chunk lies past the payload (a team wider than n / VEC) only
-// skip the loads and the store.
-template <int VEC, class Team>
-__device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecParams& P, const Rec& r,
-                                                   const GraphEnt& G) {
+// the team size and R are uniform), so both run under scalar loop control.
+// The buffer descriptors bound every access to the payload: a lane whose
+// chunk lies past it (a team wider than n / VEC) loads zeros and stores
+// nothing, and leaves the digest alone.
+template <int VEC, class Team, class Prefetch>
+__device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecParams& P, const Rec& r, uint32_t n,
+                                                   Prefetch&& prefetch) {
   typedef typename VecT<VEC>::T V;
-  const uint32_t n = G.n, S = tm.ws();
+  const uint32_t S = tm.ws();
   const uint32_t nbytes = n * 4u;
   const uint32_t npred = r.npred, R = r.rounds, tid = r.tid;
   const __amdgpu_buffer_rsrc_t wr = make_rsrc((const void*)r.out, nbytes);
   const uint32_t step = VEC * S;
-  const uint32_t chunks = uni((n + step - 1u) / step);
   uint32_t dsum = 0;
+  if (n <= step && npred - 1u < 5u) {
+    const uint32_t k0 = tm.wt() * VEC;
+    const V x = mix_rounds(V(gather5<VEC>(P, r, nbytes, k0, prefetch) ^ tid), R);
+    buf_store<VEC>(x, wr, k0 * 4);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) dsum += elem<VEC>(x, i) * (2u * (k0 + i) + 1u);
+    return k0 < n ? dsum : 0u;
+  }
+  const uint32_t chunks = uni((n + step - 1u) / step);
   for (uint32_t c = 0; c < chunks; ++c) {
     const uint32_t k0 = c * step + tm.wt() * VEC;
-    const bool valid = k0 < n;
     V acc = V(0);
-    if (valid) {
-      if (npred == 0) {
-        // source: initial payload from the graph seed
-        if constexpr (VEC == 1) {
-          acc = h32k(G.key1, ((uint64_t)tid << 16) | k0);
-        } else {
-#pragma unroll
-          for (int i = 0; i < VEC; ++i) acc[i] = h32k(G.key1, ((uint64_t)tid << 16) | (k0 + i));
-        }
+    if (npred == 0) {
+      if (c == 0) prefetch();
+      // source: initial payload from the graph seed
+      const uint64_t key = as_const(P.gtab)[r.graph].key1;
+      if constexpr (VEC == 1) {
+        acc = h32k(key, ((uint64_t)tid << 16) | k0);
       } else {
-        // groups of up to five predecessors, each group's loads issued
-        // together: one memory round trip per group, not per predecessor
-        uint32_t j = 0;
-        while (j < npred) {
-          const uint32_t m = npred - j;  // wave-uniform
-          const __amdgpu_buffer_rsrc_t r0 = make_rsrc((const void*)pred_at(P, r, j), nbytes);
-          if (m >= 5) {
-            V a0 = buf_load<VEC>(r0, k0 * 4);
-            V a1 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 1), nbytes), k0 * 4);
-            V a2 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 2), nbytes), k0 * 4);
-            V a3 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 3), nbytes), k0 * 4);
-            V a4 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 4), nbytes), k0 * 4);
-            acc += ((a0 + a1) + (a2 + a3)) + a4;
-            j += 5;
-          } else if (m == 4) {
-            V a0 = buf_load<VEC>(r0, k0 * 4);
-            V a1 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 1), nbytes), k0 * 4);
-            V a2 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 2), nbytes), k0 * 4);
-            V a3 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 3), nbytes), k0 * 4);
-            acc += (a0 + a1) + (a2 + a3);
-            j += 4;
-          } else if (m == 3) {
-            V a0 = buf_load<VEC>(r0, k0 * 4);
-            V a1 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 1), nbytes), k0 * 4);
-            V a2 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 2), nbytes), k0 * 4);
-            acc += (a0 + a1) + a2;
-            j += 3;
-          } else if (m == 2) {
-            V a0 = buf_load<VEC>(r0, k0 * 4);
-            V a1 = buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + 1), nbytes), k0 * 4);
-            acc += a0 + a1;
-            j += 2;
-          } else {
-            acc += buf_load<VEC>(r0, k0 * 4);
-            j += 1;
-          }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) acc[i] = h32k(key, ((uint64_t)tid << 16) | (k0 + i));
+      }
+    } else {
+      // groups of up to five predecessors, each group's loads issued
+      // together: one memory round trip per group, not per predecessor
+      uint32_t j = 0;
+      while (j < npred) {
+        const uint32_t m = npred - j;  // wave-uniform
+        const bool first = (c | j) == 0u;
+        auto in = [&](uint32_t i) {
+          return buf_load<VEC>(make_rsrc((const void*)pred_at(P, r, j + i), nbytes), k0 * 4);
+        };
+        if (m >= 5) {
+          const V p0 = in(0), p1 = in(1), p2 = in(2), p3 = in(3), p4 = in(4);
+          if (first) prefetch();
+          acc += ((p0 + p1) + (p2 + p3)) + p4;
+          j += 5;
+        } else if (m == 4) {
+          const V p0 = in(0), p1 = in(1), p2 = in(2), p3 = in(3);
+          if (first) prefetch();
+          acc += (p0 + p1) + (p2 + p3);
+          j += 4;
+        } else if (m == 3) {
+          const V p0 = in(0), p1 = in(1), p2 = in(2);
+          if (first) prefetch();
+          acc += (p0 + p1) + p2;
+          j += 3;
+        } else if (m == 2) {
+          const V p0 = in(0), p1 = in(1);
+          if (first) prefetch();
+          acc += p0 + p1;
+          j += 2;
+        } else {
+          const V p0 = in(0);
+          if (first) prefetch();
+          acc += p0;
+          j += 1;
         }
       }
     }
-    V x = mix_rounds(V(acc ^ tid), R);
-    if (valid) {
-      buf_store<VEC>(x, wr, k0 * 4);
+    const V x = mix_rounds(V(acc ^ tid), R);
+    buf_store<VEC>(x, wr, k0 * 4);
+    if (k0 < n) {
 #pragma unroll
       for (int i = 0; i < VEC; ++i) dsum += elem<VEC>(x, i) * (2u * (k0 + i) + 1u);
     }
@@ -299,17 +352,14 @@ __device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecPar
   return dsum;
 }
 
-// Returns the digest part of this wavefront / workgroup (the whole digest
-// unless the team is a gang).
-template <class Team>
-__device__ __forceinline__ uint32_t body_explicit(const Team& tm, const ExecParams& P, const Rec& r,
-                                                  const GraphEnt& G) {
-  const uint32_t n = G.n, S = tm.ws();
-  uint32_t dsum;
-  if (n >= 4 * S) dsum = explicit_words<4>(tm, P, r, G);
-  else if (n >= 2 * S) dsum = explicit_words<2>(tm, P, r, G);
-  else dsum = explicit_words<1>(tm, P, r, G);
-  return tm.sum(dsum);
+// Returns this lane's digest part.
+template <class Team, class Prefetch>
+__device__ __forceinline__ uint32_t body_explicit(const Team& tm, const ExecParams& P, const Rec& r, uint32_t n,
+                                                  Prefetch&& prefetch) {
+  const uint32_t S = tm.ws();
+  if (n >= 4 * S) return explicit_words<4>(tm, P, r, n, prefetch);
+  if (n >= 2 * S) return explicit_words<2>(tm, P, r, n, prefetch);
+  return explicit_words<1>(tm, P, r, n, prefetch);
 }
 
 // Elements t, t + S, t + 2S, t + 3S of p[0, len) (0 past the end).
@@ -323,26 +373,27 @@ __device__ __forceinline__ u32x4 load4(const uint32_t* p, uint32_t t, uint32_t S
   return x;
 }
 
-// Returns the digest part of this wavefront / workgroup (the whole digest
-// unless the team is a gang).  Every workgroup of a gang sums all read-only
-// elements itself; the read-write elements are split over the gang.
-template <class Team>
+// Returns this lane's digest part.  Every workgroup of a gang sums all
+// read-only elements itself; the read-write elements are split over the gang.
+template <class Team, class Prefetch>
 __device__ __forceinline__ uint32_t body_implicit(const Team& tm, const ExecParams& P, const Rec& r,
-                                                  const GraphEnt& G) {
+                                                  Prefetch&& prefetch) {
   const cptr<ReqDev> rq = as_const((const ReqDev*)r.out);
-  uint32_t* A = G.data;
+  const uint32_t nreq = rl(r.v, kDwNreq);
+  uint32_t* const A = as_const(P.gtab)[r.graph].data;
   // read-only elements: their wrap sum c
   uint32_t part = 0;
-  for (uint32_t i = 0; i < r.nreq; ++i) {
+  for (uint32_t i = 0; i < nreq; ++i) {
     const ReqDev q = rq[i];
     if (q.priv != 1) continue;
     for (uint64_t e = q.lo + tm.t; e < q.hi; e += tm.size()) part += ld_coherent(A + e);
   }
+  prefetch();
   const uint32_t key = uni(tm.sum(part) ^ r.tid);
   const uint32_t R = r.rounds;
   const uint32_t S = tm.ws(), wt = tm.wt();
   uint32_t dsum = 0;
-  for (uint32_t i = 0; i < r.nreq; ++i) {
+  for (uint32_t i = 0; i < nreq; ++i) {
     const ReqDev q = rq[i];
     if (q.priv != 2) continue;
     const uint64_t len = q.hi - q.lo;
@@ -366,51 +417,56 @@ __device__ __forceinline__ uint32_t body_implicit(const Team& tm, const ExecPara
       x = y;
     }
   }
-  return tm.sum(dsum);
+  return dsum;
 }
 
-// Run the task at `pos`; v is this lane's dword of its record.  Returns the
-// digest part of this wavefront / workgroup; run_task also stores it.
-template <class Team>
-__device__ __forceinline__ uint32_t run_body(const Team& tm, const ExecParams& P, uint32_t pos, uint32_t v, Rec& r) {
-  unpack_rec(tm, P, v, r);
-  const GraphEnt G = as_const(P.gtab)[r.graph];
-  r.digest = G.digest;
-  if (P.tstamp && tm.leader()) P.tstamp[2 * pos] = __builtin_amdgcn_s_memrealtime();
-  const uint32_t d = G.mode == 1 ? body_explicit(tm, P, r, G) : body_implicit(tm, P, r, G);
-  if (P.execs && tm.leader()) __hip_atomic_fetch_add(P.execs + pos, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+// Run the task at `pos`, whose unpacked record is r.  Returns this lane's
+// digest part.  DIAG: a diagnostic launch (start times, run counts).
+template <bool DIAG, class Team, class Prefetch>
+__device__ __forceinline__ uint32_t run_body(const Team& tm, const ExecParams& P, uint32_t pos, const Rec& r,
+                                             Prefetch&& prefetch) {
+  if (DIAG && P.tstamp && tm.leader()) P.tstamp[2 * pos] = __builtin_amdgcn_s_memrealtime();
+  const uint32_t d = (r.shape >> 24) == 1u ? body_explicit(tm, P, r, r.shape & 0xFFFFFFu, prefetch)
+                                           : body_implicit(tm, P, r, prefetch);
+  if (DIAG && P.execs && tm.leader())
+    __hip_atomic_fetch_add(P.execs + pos, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return d;
 }
 
+// Stores a task's digest: the sum of its lanes' parts.  Device-coherent, so it
+// is in memory once the leader's stores are drained.
 template <class Team>
-__device__ __forceinline__ void run_task(const Team& tm, const ExecParams& P, uint32_t pos, uint32_t v, Rec& r) {
-  const uint32_t d = run_body(tm, P, pos, v, r);
-  // device-coherent, so it is in memory once the team's stores are drained
-  // (a graph's digests may be read while its launch still runs)
+__device__ __forceinline__ void store_digest(const Team& tm, const Rec& r, uint32_t part) {
+  const uint32_t d = tm.sum(part);
   if (tm.leader()) st_coherent(r.digest + r.tid, d);
 }
 
-// Signal every out-edge of a finished task (COMPLETED_EDGE).
-template <class Team>
+// Signal one out-edge of a finished task (COMPLETED_EDGE).  Nothing waits for
+// the decrement unless doorbells are on (NOTIFY): then, for the edge that
+// empties a counter, the message that starts the task at its owner follows --
+// the owner's doorbell is rung only after the decrement has been performed (its
+// old value has returned).  The two forms are separate kernels: as a branch on
+// a parameter the compiler merged them into one returning atomic, and every
+// task waited for it (about 1100 cycles).
+template <bool NOTIFY>
 __device__ __forceinline__ void signal_edge(const ExecParams& P, uint32_t dst) {
-  if (P.notify) {
-    // COMPLETED_EDGE plus, for the edge that empties a counter, the message
-    // that starts the task at its owner: the owner's doorbell is rung only
-    // after the decrement has been performed (its old value has returned).
+  if (NOTIFY && P.notify) {
     const uint32_t old = __hip_atomic_fetch_sub(P.cnt + dst, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if ((old & kPendingMask) == 1u)
       __hip_atomic_fetch_add(P.bell + P.owner[dst] * kBellStride, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   } else {
-    __hip_atomic_fetch_sub(P.cnt + dst, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    (void)__hip_atomic_fetch_sub(P.cnt + dst, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
-template <class Team>
+template <bool NOTIFY, class Team>
 __device__ __forceinline__ void complete_edges(const Team& tm, const ExecParams& P, const Rec& r) {
   vm_drain();  // this lane's payload stores are complete
   tm.sync();   // ... and so are every other lane's of the team
-  if (tm.t < r.nsucc) signal_edge<Team>(P, r.succ0);
-  for (uint32_t j = tm.t + tm.size(); j < r.nsucc; j += tm.size()) signal_edge<Team>(P, P.succ_pos[r.succ_beg + j]);
+  if (tm.t < r.nsucc) signal_edge<NOTIFY>(P, r.succ0);
+  if (r.nsucc > tm.size())
+    for (uint32_t j = tm.t + tm.size(); j < r.nsucc; j += tm.size())
+      signal_edge<NOTIFY>(P, P.succ_pos[r.succ_beg + j]);
 }
 
 // A launch behind a pre-condition wait (k_wait_flags) does nothing if the
@@ -424,8 +480,11 @@ __device__ __forceinline__ bool gate_closed(const ExecParams& P) {
 
 constexpr uint32_t kExit = 0xFFFFFFFFu;
 
-// Per-worker scheduling state; every field holds the same value in all
-// lanes of the wave that runs the state machine.
+// Per-worker scheduling state, the same in all lanes of the wave that runs the
+// state machine, and kept in scalar registers: no branch of it may depend on a
+// lane in a way that leaves its loops (a lane-dependent report before a return
+// once did, and the compiler then kept all of this in vector registers under
+// execution masks: about 1700 cycles a task).
 struct WorkerState {
   uint32_t worker, wb, wcnt;  // list of positions [wb, wb + wcnt)
   uint32_t h;                 // first unfinished list entry
@@ -433,45 +492,66 @@ struct WorkerState {
   uint64_t pend;              // ready entries found by the last scan, not yet taken
   uint32_t seen;              // last doorbell value read
   uint32_t spins;             // consecutive empty polls
+  uint64_t now;               // clock at the last scan, or at the last task taken after it
+  bool fresh;                 // `now` is of this scan: no task taken since
   uint64_t last;              // time of the last task taken (realtime counter)
   uint64_t pub;               // time this worker last published Ctrl::progress
-  bool rescan;                // the window must be scanned before waiting
+  uint32_t stop;              // why next_task returned kExit (kGoOn: the list is finished)
   uint32_t pf_pos;            // position whose record dword is held in pf_v
   uint32_t pf_v;              // per lane: dword lane % 32 of that record
 };
+// Results of an empty poll.
+constexpr uint32_t kGoOn = 0, kLeave = 1, kStuck = 2;
 
 __device__ __forceinline__ uint64_t uni64(uint64_t x) {
   return ((uint64_t)uni((uint32_t)(x >> 32)) << 32) | uni((uint32_t)x);
 }
 
-// One poll of the ready window: every lane reads one counter and a ballot
-// collects the ready entries.  The record of the oldest unfinished entry,
-// the likeliest next task, is fetched in the same round trip (once per
-// entry), so a task that becomes ready while its worker waits for it starts
-// without another dependent load.
-__device__ __forceinline__ uint64_t ready_scan(uint32_t lane, const ExecParams& P, WorkerState& w) {
-  const uint32_t head = w.wb + w.h;
-  if (head != w.pf_pos) {
-    w.pf_v = rec_dword(P, head, lane);
-    w.pf_pos = head;
+// Fetches the record of the entry likeliest to run next: the first one found
+// ready and not yet taken, else the oldest one not taken (past the end of the
+// list, the last one again: the load is unconditional, so that the compiler
+// counts exactly how many younger loads an earlier one need not wait for).
+__device__ __forceinline__ void fetch_next(const ExecParams& P, WorkerState& w, uint32_t lane) {
+  const uint64_t u = w.pend ? w.pend : ~w.done;
+  const uint32_t e = w.h + (u ? (uint32_t)__builtin_ctzll(u) : 64u);
+  w.pf_pos = w.wb + min(e, w.wcnt - 1u);
+  w.pf_v = rec_dword(P, w.pf_pos, lane);
+}
+
+// One poll of the ready window: every lane reads one counter and ballots
+// collect the ready entries.  Lanes past the window read
+// its last counter again.  SCANREC: also fetch the record of the oldest
+// unfinished entry in the same round trip (once per entry); the wavefront
+// executor has fetched it during the task before.
+// What is left to do while the counters are on their way: `overlap`.
+template <bool SCANREC, class Overlap>
+__device__ __forceinline__ uint64_t ready_scan(uint32_t lane, const ExecParams& P, WorkerState& w,
+                                               Overlap&& overlap) {
+  const uint32_t n = min(w.wcnt - w.h, P.window);
+  const uint32_t c = ld_coherent(P.cnt + w.wb + w.h + min(lane, n - 1u));
+  if (SCANREC) {
+    const uint32_t head = w.wb + w.h;
+    if (head != w.pf_pos) {
+      w.pf_v = rec_dword(P, head, lane);
+      w.pf_pos = head;
+    }
   }
-  const uint32_t idx = w.h + lane;
-  const bool valid = lane < P.window && idx < w.wcnt && !((w.done >> lane) & 1ull);
-  uint32_t c = 1u;
-  if (valid) c = ld_coherent(P.cnt + w.wb + idx);
+  w.now = __builtin_amdgcn_s_memrealtime();
+  w.fresh = true;
+  overlap();
+  const uint64_t zero = __ballot((c & kPendingMask) == 0u) & ~w.done & (n < 64u ? (1ull << n) - 1ull : ~0ull);
   // an entry marked kAfterPrev also needs the entry before it taken (entry
   // h - 1 is finished; this worker runs its tasks one after another)
-  const bool prev_taken = lane == 0u || ((w.done >> (lane - 1u)) & 1ull);
-  return uni64(__ballot(valid && (c & kPendingMask) == 0u && (!(c & kAfterPrev) || prev_taken)));
+  return uni64(zero & (~__ballot((int)c < 0) | w.done << 1 | 1ull));
 }
 
 // Global progress: a worker that takes a task publishes the time (atomic
 // max on one word), at most once per progress_ticks, so the word is written
 // rarely however many tasks run.
-__device__ __forceinline__ void publish_progress(const ExecParams& P, WorkerState& w, uint64_t now, bool lead) {
-  if (now - w.pub < P.progress_ticks) return;
-  w.pub = now;
-  if (lead) __hip_atomic_fetch_max(&P.ctrl->progress, now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void publish_progress(const ExecParams& P, WorkerState& w, uint32_t lane) {
+  if (w.now - w.pub < P.progress_ticks) return;
+  w.pub = w.now;
+  if (lane == 0) __hip_atomic_fetch_max(&P.ctrl->progress, w.now, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // True when nothing has progressed for the watchdog interval: neither this
@@ -486,87 +566,109 @@ __device__ __forceinline__ bool stalled(const ExecParams& P, uint64_t since, uin
   return now - g > P.watchdog_ticks;
 }
 
-// Back-off after `spins` consecutive empty polls, in naps of 128 cycles: one
-// nap for the first 64 polls, then idle_sleep naps, doubling after every
-// further 64 empty polls up to 32 x idle_sleep (at most 256 naps, 14 us).  A
-// worker waiting for a quick hand-off polls again at once; one waiting behind
-// a long task soon polls only every few microseconds, and so stops taking
-// issue slots from the waves on its SIMD that run tasks (measured on 4096
-// graphs of log-normal mix rounds: 1523 ms with a fixed 2-nap back-off,
-// 1366 ms with 64 naps).
+// Back-off after `spins` consecutive empty polls, in naps of 128 cycles (55
+// ns): one nap for the first polls, then a quarter of their number up to 16,
+// so that a wake-up comes late by a small part of the wait; from the 64th on
+// idle_sleep naps (at least those 16), doubling after every further 64 empty
+// polls up to 32 x idle_sleep (at most 256 naps, 14 us).  A worker waiting for a
+// quick hand-off polls again at once; one waiting behind a long task soon polls
+// only every few microseconds, and so stops taking issue slots from the waves
+// on its SIMD that run tasks, and memory from everybody: an empty poll takes
+// 0.2 us, and thousands of workers that kept polling at that rate slowed every
+// hand-off (a 1024 x 200 stencil in level order over 8192 workers: 3.49 ms at
+// one nap a poll, 0.54 ms so).
 __device__ __forceinline__ void idle_nap(const ExecParams& P, uint32_t spins) {
-  uint32_t nap = 1;
-  if (spins >= 64) nap = min(P.idle_sleep << min((spins >> 6) - 1u, 5u), 256u);
+  uint32_t nap = max(1u, min(spins >> 2, 16u));
+  if (spins >= 64) nap = max(nap, min(P.idle_sleep << min((spins >> 6) - 1u, 5u), 256u));
   for (uint32_t i = 0; i < nap; ++i) __builtin_amdgcn_s_sleep(2);
 }
 
 // One empty poll: back off, and every 64 polls check the abort flag and the
-// watchdog.  Returns false when the worker must stop.
-__device__ __forceinline__ bool idle_step(const ExecParams& P, WorkerState& w, uint32_t lane) {
+// watchdog.
+__device__ __forceinline__ uint32_t idle_step(const ExecParams& P, WorkerState& w) {
   ++w.spins;
   idle_nap(P, w.spins);
-  if ((w.spins & 63u) != 0u) return true;
-  if (uni(ld_coherent(&P.ctrl->abort)) != 0u) return false;
+  if ((w.spins & 63u) != 0u) return kGoOn;
+  if (uni(ld_coherent(&P.ctrl->abort)) != 0u) return kLeave;
   const uint64_t now = __builtin_amdgcn_s_memrealtime();
-  if (stalled(P, w.last, now) || (P.spin_limit != 0u && w.spins >= P.spin_limit)) {
-    if (lane == 0) {
-      const uint32_t prev = __hip_atomic_fetch_add(&P.ctrl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (prev == 0u) {
-        st_coherent(&P.ctrl->stuck_worker, w.worker);
-        st_coherent(&P.ctrl->stuck_pos, w.wb + w.h);
-        st_coherent(&P.ctrl->stuck_cnt, ld_coherent(P.cnt + w.wb + w.h));
-        st_coherent(&P.ctrl->stuck_h, w.h);
-        st_coherent(&P.ctrl->stuck_wcnt, w.wcnt);
-      }
-    }
-    return false;
+  return stalled(P, w.last, now) || (P.spin_limit != 0u && w.spins >= P.spin_limit) ? kStuck : kGoOn;
+}
+
+// A worker that found no progress raises the abort flag; the first one
+// records where it was stuck.
+__device__ __forceinline__ void report_stuck(const ExecParams& P, const WorkerState& w, uint32_t lane) {
+  if (w.stop != kStuck || lane != 0) return;
+  const uint32_t prev = __hip_atomic_fetch_add(&P.ctrl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (prev == 0u) {
+    st_coherent(&P.ctrl->stuck_worker, w.worker);
+    st_coherent(&P.ctrl->stuck_pos, w.wb + w.h);
+    st_coherent(&P.ctrl->stuck_cnt, ld_coherent(P.cnt + w.wb + w.h));
+    st_coherent(&P.ctrl->stuck_h, w.h);
+    st_coherent(&P.ctrl->stuck_wcnt, w.wcnt);
   }
-  return true;
+}
+
+// Diagnostics of one poll: first and last time, number.
+__device__ __forceinline__ void stamp_scan(const ExecParams& P, const WorkerState& w, uint32_t lane) {
+  if (!P.wstamp || lane != 0) return;
+  uint64_t* ws = P.wstamp + 4 * w.worker;
+  const uint64_t now = __builtin_amdgcn_s_memrealtime();
+  if (ws[0] == 0) ws[0] = now;
+  ws[1] = now;
+  ws[2] += 1;
 }
 
 // Returns the position of the worker's next ready task, or kExit when its
-// list is finished or the launch is being aborted.  Run by one whole wave.
-__device__ uint32_t next_task(const ExecParams& P, WorkerState& w, uint32_t lane) {
+// list is finished or the launch is being aborted (w.stop says which).  Run by
+// one whole wave.  FULL: doorbells and diagnostics may be on.  The first poll
+// after a task has `overlap` to do meanwhile; the polls after it, should it find
+// nothing, are a loop of their own of few instructions, since they take issue
+// slots from the waves that run tasks.
+template <bool FULL, bool SCANREC, class Overlap>
+__device__ __forceinline__ uint32_t next_task(const ExecParams& P, WorkerState& w, uint32_t lane, Overlap&& overlap) {
   for (;;) {
     if (w.pend) {
       const uint32_t b = (uint32_t)__builtin_ctzll(w.pend);
       w.pend &= w.pend - 1;
       w.done |= 1ull << b;
       w.spins = 0;
-      w.last = __builtin_amdgcn_s_memrealtime();
-      publish_progress(P, w, w.last, lane == 0);
+      if (!w.fresh) {
+        w.now = __builtin_amdgcn_s_memrealtime();
+        overlap();
+      }
+      w.fresh = false;
+      w.last = w.now;
+      publish_progress(P, w, lane);
       return w.wb + w.h + b;
     }
     // slide the window past the finished prefix
     const uint32_t adv = (~w.done == 0ull) ? 64u : (uint32_t)__builtin_ctzll(~w.done);
     w.h += adv;
     w.done = adv >= 64u ? 0ull : (w.done >> adv);
-    if (adv) w.rescan = true;
     if (w.h >= w.wcnt) return kExit;
-    if (P.notify && !w.rescan) {
-      // wait for a message: one word per poll instead of the whole window
-      const uint32_t b = uni(ld_coherent(P.bell + w.worker * kBellStride));
-      if (b == w.seen) {
-        if (!idle_step(P, w, lane)) return kExit;
-        continue;
+    w.pend = ready_scan<SCANREC>(lane, P, w, overlap);
+    if (FULL) stamp_scan(P, w, lane);
+    while (!w.pend) {
+      if (FULL && P.notify) {
+        // wait for a message: one word per poll instead of the whole window
+        // (a message rung before the last scan shows as a new value here, and
+        // costs one scan)
+        for (;;) {
+          const uint32_t b = uni(ld_coherent(P.bell + w.worker * kBellStride));
+          if (b != w.seen) {
+            w.seen = b;
+            break;
+          }
+          w.stop = idle_step(P, w);
+          if (w.stop != kGoOn) return kExit;
+        }
+      } else {
+        w.stop = idle_step(P, w);
+        if (w.stop != kGoOn) return kExit;
       }
-      w.seen = b;
+      w.pend = ready_scan<SCANREC>(lane, P, w, [] {});
+      if (FULL) stamp_scan(P, w, lane);
     }
-    w.pend = ready_scan(lane, P, w);
-    if (P.wstamp && lane == 0) {
-      uint64_t* ws = P.wstamp + 4 * w.worker;
-      const uint64_t now = __builtin_amdgcn_s_memrealtime();
-      if (ws[0] == 0) ws[0] = now;
-      ws[1] = now;
-      ws[2] += 1;
-    }
-    if (w.pend) {
-      w.rescan = true;
-      continue;
-    }
-    w.rescan = false;
-    if (P.notify) continue;
-    if (!idle_step(P, w, lane)) return kExit;
   }
 }
 
@@ -598,36 +700,67 @@ __device__ __forceinline__ void worker_init(WorkerState& w, const ExecParams& P,
   w.pend = 0;
   w.seen = 0;
   w.spins = 0;
-  w.last = __builtin_amdgcn_s_memrealtime();
+  w.now = w.last = __builtin_amdgcn_s_memrealtime();
+  w.fresh = false;
   w.pub = 0;
-  w.rescan = true;
+  w.stop = kGoOn;
   w.pf_pos = kExit;
   w.pf_v = 0;
 }
 
+// One wavefront per task.  A task's chain of memory round trips is: counters
+// back (and the signals of the task before acknowledged: loads return in order
+// behind them), payloads back, stores drained, signals out.  Everything else
+// runs while one of them is under way: the record of the next task is fetched
+// behind the payload loads and unpacked behind the next poll, and the digest,
+// which no other task reads, is reduced and stored there too.
+template <bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_exec_wave(ExecParams P) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t worker = uni((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   if (worker >= P.nworkers || gate_closed(P)) return;
   const WaveTeam tm{lane};
-  if (P.diag && lane == 0) __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (FULL && P.diag && lane == 0)
+    __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   WorkerState w;
   worker_init(w, P, worker);
+  if (w.wcnt) fetch_next(P, w, lane);
+  Rec r;                     // the task being run, then the next one
+  uint32_t r_pos = kExit;    // position of the record in r
+  uint32_t part = 0;         // digest part of the last task, until it is stored ...
+  uint32_t* part_of = nullptr;  // ... here (null: stored)
+  // The store is issued whether or not there is a digest (to no lane then, by
+  // the descriptor's bounds), so that the compiler counts it and does not wait
+  // for it where it waits for the poll before it.
+  auto overlap = [&] {
+    buf_store<1>(tm.sum(part), make_rsrc(part_of, part_of ? 4u : 0u), lane * 4u);
+    part_of = nullptr;
+    if (r_pos != w.pf_pos) {
+      unpack_rec(tm, P, w.pf_v, r);
+      r_pos = w.pf_pos;
+    }
+  };
   for (;;) {
-    const uint32_t pos = next_task(P, w, lane);
+    const uint32_t pos = next_task<FULL, false>(P, w, lane, overlap);
     if (pos == kExit) break;
-    const uint32_t v = pos == w.pf_pos ? w.pf_v : rec_dword(P, pos, lane);
-    Rec r;
-    run_task(tm, P, pos, v, r);
-    complete_edges(tm, P, r);
-    if (P.tstamp && lane == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
+    if (pos != r_pos) {
+      unpack_rec(tm, P, rec_dword(P, pos, lane), r);
+      r_pos = pos;
+    }
+    part = run_body<FULL>(tm, P, pos, r, [&] { fetch_next(P, w, lane); });
+    complete_edges<FULL>(tm, P, r);
+    part_of = r.digest + r.tid;
+    if (FULL && P.tstamp && lane == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
   }
-  if (P.wprog && lane == 0) P.wprog[worker] = w.h;
+  buf_store<1>(tm.sum(part), make_rsrc(part_of, part_of ? 4u : 0u), lane * 4u);
+  report_stuck(P, w, lane);
+  if (FULL && P.wprog && lane == 0) P.wprog[worker] = w.h;
 }
 
 // One workgroup per task: wave 0 runs the scheduling state machine and
 // stages the chosen position and its record in LDS; every wave then executes
 // the same sequence of barriers for each task.
+template <bool FULL>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_exec_block(ExecParams P) {
   __shared__ uint32_t lds[32];
   __shared__ uint32_t cmd;
@@ -635,14 +768,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   const uint32_t worker = blockIdx.x;
   if (worker >= P.nworkers || gate_closed(P)) return;
   const BlockTeam tm{threadIdx.x, blockDim.x, lds};
-  const uint32_t lane = threadIdx.x & 63u;
-  if (P.diag && threadIdx.x == 0)
+  const uint32_t lane = threadIdx.x & 63u, wave = uni(threadIdx.x >> 6);
+  if (FULL && P.diag && threadIdx.x == 0)
     __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   WorkerState w;
   worker_init(w, P, worker);
   for (;;) {
-    if (threadIdx.x < 64) {
-      const uint32_t pos = next_task(P, w, lane);
+    if (wave == 0) {
+      const uint32_t pos = next_task<FULL, true>(P, w, lane, [] {});
       if (pos != kExit) {
         const uint32_t v = pos == w.pf_pos ? w.pf_v : rec_dword(P, pos, lane);
         if (lane < 32) recl[lane] = v;
@@ -655,12 +788,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     __syncthreads();
     if (pos == kExit) break;
     Rec r;
-    run_task(tm, P, pos, v, r);
-    complete_edges(tm, P, r);
-    if (P.tstamp && threadIdx.x == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
+    unpack_rec(tm, P, v, r);
+    const uint32_t part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
+    complete_edges<FULL>(tm, P, r);
+    store_digest(tm, r, part);
+    if (FULL && P.tstamp && threadIdx.x == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
     __syncthreads();
   }
-  if (P.wprog && threadIdx.x == 0) P.wprog[worker] = w.h;
+  if (wave == 0) report_stuck(P, w, lane);
+  if (FULL && P.wprog && threadIdx.x == 0) P.wprog[worker] = w.h;
 }
 
 // A gang of P.gang workgroups per task (on different CUs), without a leader:
@@ -673,6 +809,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
 // different tasks of the list at the same time (each takes its ready entries
 // in its own order), and none of the mailbox round trips a leader would need
 // (publish the task, collect the arrivals) sits between two dependent tasks.
+template <bool FULL>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_exec_gang(ExecParams P) {
   __shared__ uint32_t lds[32];
   __shared__ uint32_t cmd;
@@ -686,12 +823,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   tm.lds = lds;
   tm.m = member;
   tm.G = G;
-  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t lane = threadIdx.x & 63u, wave = uni(threadIdx.x >> 6);
   WorkerState w;
   worker_init(w, P, gang);
   for (;;) {
-    if (threadIdx.x < 64) {
-      const uint32_t pos = next_task(P, w, lane);
+    if (wave == 0) {
+      const uint32_t pos = next_task<FULL, true>(P, w, lane, [] {});
       if (pos != kExit) {
         const uint32_t v = pos == w.pf_pos ? w.pf_v : rec_dword(P, pos, lane);
         if (lane < 32) recl[lane] = v;
@@ -704,16 +841,20 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     __syncthreads();
     if (pos == kExit) break;
     Rec r;
-    const uint32_t d = run_body(tm, P, pos, v, r);
-    if (threadIdx.x == 0) __hip_atomic_fetch_add(r.digest + r.tid, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    complete_edges(tm, P, r);
+    unpack_rec(tm, P, v, r);
+    const uint32_t part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
+    complete_edges<FULL>(tm, P, r);
+    const uint32_t d = tm.sum(part);
+    if (threadIdx.x == 0)
+      __hip_atomic_fetch_add(r.digest + r.tid, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     // diagnostics: a task ends when its last member finishes
-    if (P.tstamp && threadIdx.x == 0)
+    if (FULL && P.tstamp && threadIdx.x == 0)
       __hip_atomic_fetch_max(P.tstamp + 2 * pos + 1, __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
   }
-  if (member == 0 && P.wprog && threadIdx.x == 0) P.wprog[gang] = w.h;
+  if (wave == 0) report_stuck(P, w, lane);
+  if (FULL && member == 0 && P.wprog && threadIdx.x == 0) P.wprog[gang] = w.h;
 }
 
 // ------------------------------------------------------ ready-queue dispatch
@@ -748,6 +889,8 @@ struct QueueState {
   uint32_t tile_h, tile_n, tile_i; // claimed tickets [tile_h, tile_h + tile_n), next tile_i
   uint32_t sinks;                  // sinks finished since the last report
   uint64_t pub;                    // time this worker last published Ctrl::progress
+  uint32_t stop;                   // kStuck: queue_next gave up at ticket `stuck`
+  uint32_t stuck;
 };
 
 __device__ __forceinline__ uint32_t* q_head(const ExecParams& P, uint32_t s) { return P.qctl + s * kQLine; }
@@ -765,6 +908,8 @@ __device__ __forceinline__ void queue_init(QueueState& q, const ExecParams& P, u
   q.tile_h = q.tile_n = q.tile_i = 0;
   q.sinks = 0;
   q.pub = 0;
+  q.stop = kGoOn;
+  q.stuck = 0;
 }
 
 // Raises the abort flag; the first abort records where it happened.
@@ -812,8 +957,9 @@ __device__ __forceinline__ void queue_progress(const ExecParams& P, QueueState& 
 }
 
 // Position of the worker's next task, or kExit at the end of the launch (or
-// when it is being aborted).  Run by one whole wave.
-__device__ uint32_t queue_next(const ExecParams& P, QueueState& q, uint32_t lane) {
+// when it is being aborted: q.stop).  Run by one whole wave; like next_task,
+// no lane-dependent branch leaves its loop.
+__device__ __forceinline__ uint32_t queue_next(const ExecParams& P, QueueState& q, uint32_t lane) {
   if (q.local != kExit) {
     const uint32_t pos = q.local;
     q.local = kExit;
@@ -829,7 +975,8 @@ __device__ uint32_t queue_next(const ExecParams& P, QueueState& q, uint32_t lane
   }
   const uint32_t t = q.tile_h + q.tile_i;
   if (t >= P.qcap) {  // beyond every sentinel: the protocol's bound was broken
-    queue_abort(P, q, lane, t);
+    q.stop = kStuck;
+    q.stuck = t;
     return kExit;
   }
   const uint32_t* slot = P.q + (size_t)q.shard * P.qcap + t;
@@ -840,16 +987,18 @@ __device__ uint32_t queue_next(const ExecParams& P, QueueState& q, uint32_t lane
     // a fixed back-off here, not the growing one of the lists: a queue
     // worker waits for whichever task is pushed next, and in the serving
     // loop a late claim delays a request (median latency 9.7 ms with the
-    // fixed back-off, 11.4 ms with the growing one, same box)
+    // fixed back-off, 11.4 ms with the growing one, same box).  Four naps (0.2
+    // us) a poll: stencil 1024 x 500 1.76 ms, with one nap 1.80, with 16 1.83
     for (uint32_t spins = 1;; ++spins) {
-      const uint32_t nap = spins < 64 ? 1u : P.idle_sleep;
+      const uint32_t nap = spins < 64 ? 4u : max(P.idle_sleep, 4u);
       for (uint32_t i = 0; i < nap; ++i) __builtin_amdgcn_s_sleep(2);
       v = uni(ld_coherent(slot));
       if (v != kQEmpty) break;
       if ((spins & 63u) == 0u) {
         if (uni(ld_coherent(&P.ctrl->abort)) != 0u) return kExit;
         if (stalled(P, t0, __builtin_amdgcn_s_memrealtime()) || (P.spin_limit != 0u && spins >= P.spin_limit)) {
-          queue_abort(P, q, lane, t);
+          q.stop = kStuck;
+          q.stuck = t;
           return kExit;
         }
       }
@@ -927,28 +1076,39 @@ __device__ __forceinline__ void graph_sink_done(const ExecParams& P, uint32_t gr
     __hip_atomic_store(P.gflag + graph, P.gseq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// With per-graph completion a digest is stored before the store drain, so that
+// a graph's digests are in memory once its last sink has been counted; else
+// after the edge signals, which do not wait for its reduction then (random
+// pattern 1024 x 50: 242 against 258 us).
+template <bool FULL>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_exec_wave_q(ExecParams P) {
   const uint32_t lane = threadIdx.x & 63u;
   const uint32_t worker = uni((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   if (worker >= P.nworkers || gate_closed(P)) return;
   const WaveTeam tm{lane};
-  if (P.diag && lane == 0) __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (FULL && P.diag && lane == 0)
+    __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   QueueState q;
   queue_init(q, P, worker);
   for (;;) {
     const uint32_t pos = queue_next(P, q, lane);
     if (pos == kExit) break;
     Rec r;
-    run_task(tm, P, pos, rec_dword(P, pos, lane), r);
+    unpack_rec(tm, P, rec_dword(P, pos, lane), r);
+    const uint32_t part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
+    if (P.gdone) store_digest(tm, r, part);
     if (r.nsucc == 0u) ++q.sinks;
     complete_edges_q(tm, P, r, q, true);
+    if (!P.gdone) store_digest(tm, r, part);
     if (r.nsucc == 0u) graph_sink_done(P, r.graph, lane == 0);
-    if (P.tstamp && lane == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
+    if (FULL && P.tstamp && lane == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
   }
+  if (q.stop == kStuck) queue_abort(P, q, lane, q.stuck);
 }
 
 // One workgroup per task: wave 0 takes the tasks and stages the record in
 // LDS; every wave pushes the successors its lanes made ready.
+template <bool FULL>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_exec_block_q(ExecParams P) {
   __shared__ uint32_t lds[32];
   __shared__ uint32_t cmd;
@@ -956,13 +1116,13 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   const uint32_t worker = blockIdx.x;
   if (worker >= P.nworkers || gate_closed(P)) return;
   const BlockTeam tm{threadIdx.x, blockDim.x, lds};
-  const uint32_t lane = threadIdx.x & 63u;
-  if (P.diag && threadIdx.x == 0)
+  const uint32_t lane = threadIdx.x & 63u, wave = uni(threadIdx.x >> 6);
+  if (FULL && P.diag && threadIdx.x == 0)
     __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   QueueState q;
   queue_init(q, P, worker);
   for (;;) {
-    if (threadIdx.x < 64) {
+    if (wave == 0) {
       const uint32_t pos = queue_next(P, q, lane);
       if (pos != kExit && lane < 32) recl[lane] = rec_dword(P, pos, lane);
       if (lane == 0) cmd = pos;
@@ -973,13 +1133,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     __syncthreads();
     if (pos == kExit) break;
     Rec r;
-    run_task(tm, P, pos, v, r);
-    if (threadIdx.x < 64 && r.nsucc == 0u) ++q.sinks;
-    complete_edges_q(tm, P, r, q, threadIdx.x < 64);
+    unpack_rec(tm, P, v, r);
+    const uint32_t part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
+    if (P.gdone) store_digest(tm, r, part);
+    if (wave == 0 && r.nsucc == 0u) ++q.sinks;
+    complete_edges_q(tm, P, r, q, wave == 0);
+    if (!P.gdone) store_digest(tm, r, part);
     if (r.nsucc == 0u) graph_sink_done(P, r.graph, threadIdx.x == 0);
-    if (P.tstamp && threadIdx.x == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
+    if (FULL && P.tstamp && threadIdx.x == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
     __syncthreads();
   }
+  if (wave == 0 && q.stop == kStuck) queue_abort(P, q, lane, q.stuck);
 }
 
 // Empties the slots the previous launch filled: [0, tail) of every shard
@@ -1058,7 +1222,9 @@ __global__ __launch_bounds__(256) void k_reset(ExecParams P) {
 __global__ __launch_bounds__(64) void k_one_task(ExecParams P, uint32_t pos) {
   const WaveTeam tm{threadIdx.x};
   Rec r;
-  run_task(tm, P, pos, rec_dword(P, pos, threadIdx.x), r);
+  unpack_rec(tm, P, rec_dword(P, pos, threadIdx.x), r);
+  const uint32_t part = run_body<false>(tm, P, pos, r, NoPrefetch());
+  store_digest(tm, r, part);
 }
 
 // -------------------------------------------- records built on the device
@@ -1094,6 +1260,7 @@ __global__ __launch_bounds__(256) void k_build_records(const GraphSrc* gsrc, uin
     r.tid = v;
     r.graph = gi;
     r.rounds = g.rounds[v];
+    r.shape = task_shape(g.mode, g.mode == 1 ? g.n : 0u);
     const uint64_t wbytes = (uint64_t)g.n * 4u;
     // the inline lists are filled with constant indices so that the record
     // stays in registers (a variable index would put it in scratch memory)
@@ -1211,17 +1378,23 @@ hipError_t launch_reset(const ExecParams& p, hipStream_t s) {
   return hipGetLastError();
 }
 
+// The kernels come in two forms: with doorbells or diagnostics, and without.
 hipError_t launch_exec(const ExecParams& p, uint32_t mapping, uint32_t wg_waves, uint32_t grid_blocks,
                        hipStream_t s) {
+  const bool full = p.notify || p.diag;
+  const dim3 grid(grid_blocks), wave(256), block(wg_waves * 64u);
   if (p.residency_probe) {
-    if (mapping == 1) hipLaunchKernelGGL(k_probe_wave, dim3(grid_blocks), dim3(256), 0, s, p);
-    else hipLaunchKernelGGL(k_probe_block, dim3(grid_blocks), dim3(wg_waves * 64u), 0, s, p);
+    if (mapping == 1) hipLaunchKernelGGL(k_probe_wave, grid, wave, 0, s, p);
+    else hipLaunchKernelGGL(k_probe_block, grid, block, 0, s, p);
   } else if (mapping == 1) {
-    hipLaunchKernelGGL(k_exec_wave, dim3(grid_blocks), dim3(256), 0, s, p);
+    if (full) hipLaunchKernelGGL(k_exec_wave<true>, grid, wave, 0, s, p);
+    else hipLaunchKernelGGL(k_exec_wave<false>, grid, wave, 0, s, p);
   } else if (mapping == 2) {
-    hipLaunchKernelGGL(k_exec_block, dim3(grid_blocks), dim3(wg_waves * 64u), 0, s, p);
+    if (full) hipLaunchKernelGGL(k_exec_block<true>, grid, block, 0, s, p);
+    else hipLaunchKernelGGL(k_exec_block<false>, grid, block, 0, s, p);
   } else {
-    hipLaunchKernelGGL(k_exec_gang, dim3(grid_blocks), dim3(wg_waves * 64u), 0, s, p);
+    if (full) hipLaunchKernelGGL(k_exec_gang<true>, grid, block, 0, s, p);
+    else hipLaunchKernelGGL(k_exec_gang<false>, grid, block, 0, s, p);
   }
   return hipGetLastError();
 }
@@ -1250,16 +1423,23 @@ hipError_t launch_queue_reset(const ExecParams& p, hipStream_t s) {
 
 hipError_t launch_exec_queue(const ExecParams& p, uint32_t mapping, uint32_t wg_waves, uint32_t grid_blocks,
                              hipStream_t s) {
-  if (mapping == 1) hipLaunchKernelGGL(k_exec_wave_q, dim3(grid_blocks), dim3(256), 0, s, p);
-  else hipLaunchKernelGGL(k_exec_block_q, dim3(grid_blocks), dim3(wg_waves * 64u), 0, s, p);
+  const dim3 grid(grid_blocks), wave(256), block(wg_waves * 64u);
+  if (mapping == 1) {
+    if (p.diag) hipLaunchKernelGGL(k_exec_wave_q<true>, grid, wave, 0, s, p);
+    else hipLaunchKernelGGL(k_exec_wave_q<false>, grid, wave, 0, s, p);
+  } else {
+    if (p.diag) hipLaunchKernelGGL(k_exec_block_q<true>, grid, block, 0, s, p);
+    else hipLaunchKernelGGL(k_exec_block_q<false>, grid, block, 0, s, p);
+  }
   return hipGetLastError();
 }
 
 int exec_blocks_per_cu(uint32_t mapping, uint32_t wg_waves) {
   int nb = 0;
   hipError_t e;
-  if (mapping == 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_exec_wave, 256, 0);
-  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_exec_block, (int)(wg_waves * 64u), 0);
+  // (both forms are held to eight wavefronts a SIMD)
+  if (mapping == 1) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_exec_wave<true>, 256, 0);
+  else e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, k_exec_block<true>, (int)(wg_waves * 64u), 0);
   if (e != hipSuccess) return -1;
   return nb;
 }
