@@ -108,7 +108,10 @@ typedef struct {
  *                  every further 64 empty polls, up to 32 times this value (at
  *                  most 256 units).
  *   schedule     : how tasks are partitioned over the workers' lists
- *                  (Algorithm 1, Compile): TG_SCHED_LEVEL (default) sorts by
+ *                  (Algorithm 1, Compile); by default TG_SCHED_COLUMN for one
+ *                  graph on wavefronts or workgroups whose `workers` is 0
+ *                  too, else TG_SCHED_LEVEL.
+ *                  TG_SCHED_LEVEL sorts by
  *                  dependence level and deals round-robin; TG_SCHED_SPREAD
  *                  stretches every graph's levels over the same interval
  *                  before sorting and dealing, so graphs of different depths
@@ -458,7 +461,7 @@ tg_status tg_exec_occupancy(uint32_t mapping, uint32_t wg_waves, uint32_t* block
 tg_status tg_graph_exec_info(tg_graph g, uint32_t* workers, uint32_t* started);
 /* Host-only model of a launch of graphs[0..ngraphs) together (one graph
  * alone, or a batch), no GPU needed: compiles the worker layout for nworkers
- * workers with the given schedule (0 = default) and steps the same
+ * workers with the given schedule (0 = TG_SCHED_LEVEL) and steps the same
  * ready-window loop as the kernels in a seeded order.  order (total #tasks
  * entries) receives the execution order as (graph index << 32 | event),
  * *executed the number of tasks run; TG_ETIMEOUT if the layout would
@@ -484,7 +487,7 @@ tg_status tg_emulate_queue(const tg_graph* graphs, uint32_t ngraphs, uint32_t nw
                            uint64_t seed, uint64_t* order, uint64_t* executed);
 /* Host-only model of a gang launch (mapping 3, Algorithm 1 EXECUTE_OP with
  * one task per gang of workgroups) over graphs[0..ngraphs): ngangs lists
- * compiled with `schedule` (0 = default), and `gang` members per list that
+ * compiled with `schedule` (0 = TG_SCHED_LEVEL), and `gang` members per list that
  * each scan, take and finish their share on their own, in a seeded
  * interleaving; a counter starts at in-degree x gang and each member
  * decrements every out-edge once.  Checks that a member takes a task only
