@@ -266,6 +266,52 @@ __device__ __forceinline__ typename VecT<VEC>::T gather5(const ExecParams& P, co
   return ((p0 + p1) + (p2 + p3)) + p4;
 }
 
+// A task of NP predecessors whose payload takes several chunks, two chunks at
+// a time: the loads of both are in flight together, so a payload costs one
+// memory round trip per two chunks.  Up to three predecessors, whose two chunks
+// take 24 vector registers; four or five would spill.  192 x 40 stencil tasks of
+// 64 KiB (about 0.2 ms of traffic) take 415 us on four wavefronts each, 749 us
+// one chunk at a time; 512 x 200 of 4 KiB on one wavefront 543 and 975 us.
+// Issuing the next pair's loads before this pair's mix as well spills too: 367
+// us for the former, 635 us for the latter.
+template <int VEC, int NP, class Team, class Prefetch>
+__device__ __forceinline__ uint32_t explicit_chunks(const Team& tm, const ExecParams& P, const Rec& r, uint32_t n,
+                                                    Prefetch&& prefetch) {
+  typedef typename VecT<VEC>::T V;
+  const uint32_t nbytes = n * 4u, step = VEC * tm.ws();
+  const uint32_t pairs = uni((n + 2u * step - 1u) / (2u * step));
+  uint32_t k0 = tm.wt() * VEC, dsum = 0;
+  for (uint32_t c = 0; c < pairs; ++c) {
+    V p[NP], q[NP];
+#pragma unroll
+    for (int j = 0; j < NP; ++j) {
+      const __amdgpu_buffer_rsrc_t in = make_rsrc((const void*)pred_at(P, r, j), nbytes);
+      p[j] = buf_load<VEC>(in, k0 * 4u);
+      q[j] = buf_load<VEC>(in, (k0 + step) * 4u);
+    }
+    if (c == 0) prefetch();
+#pragma unroll
+    for (int j = 1; j < NP; ++j) {
+      p[0] += p[j];
+      q[0] += q[j];
+    }
+    const __amdgpu_buffer_rsrc_t wr = make_rsrc((const void*)r.out, nbytes);
+    const V x = mix_rounds(V(p[0] ^ r.tid), r.rounds);
+    buf_store<VEC>(x, wr, k0 * 4u);
+    const V y = mix_rounds(V(q[0] ^ r.tid), r.rounds);
+    buf_store<VEC>(y, wr, (k0 + step) * 4u);
+    uint32_t dx = 0, dy = 0;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+      dx += elem<VEC>(x, i) * (2u * (k0 + i) + 1u);
+      dy += elem<VEC>(y, i) * (2u * (k0 + step + i) + 1u);
+    }
+    dsum += (k0 < n ? dx : 0u) + (k0 + step < n ? dy : 0u);
+    k0 += 2u * step;
+  }
+  return dsum;
+}
+
 // Explicit body over words k = k0, k0 + VEC*S, ... handled VEC at a time.
 // The chunk loop and the mix-round loop have wave-uniform trip counts (n,
 // the team size and R are uniform), so both run under scalar loop control.
@@ -290,6 +336,12 @@ __device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecPar
     for (int i = 0; i < VEC; ++i) dsum += elem<VEC>(x, i) * (2u * (k0 + i) + 1u);
     return k0 < n ? dsum : 0u;
   }
+  if constexpr (VEC == 4)  // (narrower vectors: at most one chunk and a half)
+    if (npred - 1u < 3u) {
+      if (npred == 1) return explicit_chunks<VEC, 1>(tm, P, r, n, prefetch);
+      if (npred == 2) return explicit_chunks<VEC, 2>(tm, P, r, n, prefetch);
+      return explicit_chunks<VEC, 3>(tm, P, r, n, prefetch);
+    }
   const uint32_t chunks = uni((n + step - 1u) / step);
   for (uint32_t c = 0; c < chunks; ++c) {
     const uint32_t k0 = c * step + tm.wt() * VEC;

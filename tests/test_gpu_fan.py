@@ -16,6 +16,7 @@ SHAPES = {
     "one worker": dict(mapping=1, workers=1),
     "columns": dict(mapping=1, schedule=tg.TG_SCHED_COLUMN, window=1),
     "workgroup": dict(mapping=2, wg_waves=2),
+    "workgroup of three": dict(mapping=2, wg_waves=3),  # chunks that do not divide a payload
     "gang": dict(mapping=3, wg_waves=2, gang=2),
     "queue": dict(mapping=1, dispatch=tg.TG_DISPATCH_QUEUE),
     "queue, workgroup": dict(mapping=2, wg_waves=2, dispatch=tg.TG_DISPATCH_QUEUE),
