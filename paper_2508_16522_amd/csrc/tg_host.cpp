@@ -372,7 +372,10 @@ struct tg_graph_s {
   // execution state
   bool inflight = false;
   Layout* last_layout = nullptr;
-  hipEvent_t ev0 = nullptr, ev1 = nullptr, evk = nullptr;
+  hipEvent_t ev0 = nullptr, ev1 = nullptr;  // start of the last execution; end of a comparator's
+                                            // or of a launch that sets a flag
+  hipEvent_t evk = nullptr, evd = nullptr;  // start and end of the last launch's executor (one of
+                                            // the ring's, or ev1): not owned
   double compile_ms = 0, infer_ms = 0, exec_ms = 0, kernel_ms = 0;
   bool has_tuned = false;
   tg_exec_config tuned{};
@@ -399,7 +402,8 @@ struct tg_batch_s {
   std::shared_ptr<PlanCache> plans;
   bool inflight = false;
   hipStream_t last_stream = nullptr;
-  hipEvent_t ev0 = nullptr, ev1 = nullptr;
+  hipEvent_t ev0 = nullptr, evd = nullptr;  // start of the last execution; its end (one of the
+                                            // ring's: not owned)
   static constexpr uint32_t kRing = 64;
   hipEvent_t rk0[kRing] = {}, rk1[kRing] = {};
   uint64_t launches = 0;
@@ -1904,9 +1908,13 @@ struct LaunchConds {
   uint32_t post_value = 0;
 };
 
+// ring0, ring1: recorded around the executor kernel (may be null).  *done, if
+// asked for, is the event that marks the end of the launch: ring1, unless a
+// post-condition flag follows it.  An event record costs the host about 4 us
+// and the stream a packet between the kernels, so one serves every reader.
 tg_status launch_layout(Layout& L, const Config& cfg, const std::vector<tg_graph>& gs, hipStream_t st,
-                        hipEvent_t before_kernel = nullptr, hipEvent_t ring0 = nullptr, hipEvent_t ring1 = nullptr,
-                        const LaunchConds* conds = nullptr) {
+                        hipEvent_t ring0 = nullptr, hipEvent_t ring1 = nullptr, const LaunchConds* conds = nullptr,
+                        hipEvent_t after_flag = nullptr, hipEvent_t* done = nullptr) {
   std::lock_guard<std::mutex> ledger_lk(g_ledger_mu);
   for (size_t i = 0; i < g_flights.size();) {
     if (g_flights[i].key != &L && hipEventQuery(g_flight_ev[i]) == hipErrorNotReady) {
@@ -1961,17 +1969,22 @@ tg_status launch_layout(Layout& L, const Config& cfg, const std::vector<tg_graph
   if (queue) HIPCHK(tg::launch_queue_reset(P, st));
   P.gated = conds && conds->pre.n ? 1u : 0u;
   if (P.gated) HIPCHK(tg::launch_wait_flags(conds->pre, P.ctrl, P.watchdog_ticks, st));
-  if (before_kernel) HIPCHK(hipEventRecord(before_kernel, st));
   if (ring0) HIPCHK(hipEventRecord(ring0, st));
   if (L.npos) {
     if (queue) HIPCHK(tg::launch_exec_queue(P, cfg.mapping, cfg.wg_waves, L.grid_blocks, st));
     else HIPCHK(tg::launch_exec(P, cfg.mapping, cfg.wg_waves, L.grid_blocks, st));
   }
   if (ring1) HIPCHK(hipEventRecord(ring1, st));
-  if (conds && conds->post) HIPCHK(tg::launch_set_flag(conds->post, conds->post_value, P.ctrl, st));
-  HIPCHK(hipEventRecord(L.ev_done, st));
+  hipEvent_t end = ring1;
+  if (conds && conds->post) {
+    HIPCHK(tg::launch_set_flag(conds->post, conds->post_value, P.ctrl, st));
+    end = after_flag;
+  }
+  if (!end) end = L.ev_done;
+  if (end != ring1) HIPCHK(hipEventRecord(end, st));
+  if (done) *done = end;
   g_flights.push_back(me);
-  g_flight_ev.push_back(L.ev_done);
+  g_flight_ev.push_back(end);
   return TG_OK;
 }
 
@@ -2004,11 +2017,11 @@ tg_status check_abort(Layout* L) {
 tg_status graph_wait(tg_graph g) {
   if (!g->inflight) return TG_OK;
   g->inflight = false;
-  HIPCHK(hipEventSynchronize(g->ev1));
+  HIPCHK(hipEventSynchronize(g->evd));
   float ms = 0;
-  if (hipEventElapsedTime(&ms, g->ev0, g->ev1) == hipSuccess) g->exec_ms = ms;
+  if (hipEventElapsedTime(&ms, g->ev0, g->evd) == hipSuccess) g->exec_ms = ms;
   g->kernel_ms = 0;
-  if (g->last_layout && hipEventElapsedTime(&ms, g->evk, g->ev1) == hipSuccess) g->kernel_ms = ms;
+  if (g->last_layout && hipEventElapsedTime(&ms, g->evk, g->evd) == hipSuccess) g->kernel_ms = ms;
   (void)hipGetLastError();
   return check_abort(g->last_layout);
 }
@@ -2261,7 +2274,6 @@ void drop_solo(tg_graph g) {
 tg_status ensure_events(tg_graph g) {
   if (!g->ev0) HIPCHK(hipEventCreate(&g->ev0));
   if (!g->ev1) HIPCHK(hipEventCreate(&g->ev1));
-  if (!g->evk) HIPCHK(hipEventCreate(&g->evk));
   if (!g->rk0[0])
     for (uint32_t i = 0; i < tg_graph_s::kRing; ++i) {
       HIPCHK(hipEventCreate(&g->rk0[i]));
@@ -2490,8 +2502,8 @@ static tg_status graph_execute(tg_graph g, const tg_exec_config* cfgp, void* str
   HIPCHK(hipEventRecord(g->ev0, st));
   std::vector<tg_graph> gs{g};
   const uint32_t slot = (uint32_t)(g->launches % tg_graph_s::kRing);
-  if ((s = launch_layout(*g->solo, cfg, gs, st, g->evk, g->rk0[slot], g->rk1[slot], conds)) != TG_OK) return s;
-  HIPCHK(hipEventRecord(g->ev1, st));
+  if ((s = launch_layout(*g->solo, cfg, gs, st, g->rk0[slot], g->rk1[slot], conds, g->ev1, &g->evd)) != TG_OK) return s;
+  g->evk = g->rk0[slot];
   g->launches++;
   g->inflight = true;
   g->last_stream = st;
@@ -3090,7 +3102,6 @@ tg_status tg_graph_destroy(tg_graph g) {
   drop_solo(g);
   if (g->ev0) (void)hipEventDestroy(g->ev0);
   if (g->ev1) (void)hipEventDestroy(g->ev1);
-  if (g->evk) (void)hipEventDestroy(g->evk);
   for (uint32_t i = 0; i < tg_graph_s::kRing; ++i) {
     if (g->rk0[i]) (void)hipEventDestroy(g->rk0[i]);
     if (g->rk1[i]) (void)hipEventDestroy(g->rk1[i]);
@@ -3117,7 +3128,6 @@ tg_status tg_batch_create(tg_batch* out, const tg_graph* graphs, uint32_t n, con
   if (s != TG_OK) return s;
   for (auto g : gs) b->gens.push_back(g->dev_gen);
   HIPCHK(hipEventCreate(&b->ev0));
-  HIPCHK(hipEventCreate(&b->ev1));
   for (uint32_t i = 0; i < tg_batch_s::kRing; ++i) {
     HIPCHK(hipEventCreate(&b->rk0[i]));
     HIPCHK(hipEventCreate(&b->rk1[i]));
@@ -3143,9 +3153,8 @@ tg_status tg_batch_execute(tg_batch b, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   HIPCHK(hipEventRecord(b->ev0, st));
   const uint32_t slot = (uint32_t)(b->launches % tg_batch_s::kRing);
-  tg_status s = launch_layout(*b->lay, b->lay->cfg, b->graphs, st, nullptr, b->rk0[slot], b->rk1[slot]);
+  tg_status s = launch_layout(*b->lay, b->lay->cfg, b->graphs, st, b->rk0[slot], b->rk1[slot], nullptr, nullptr, &b->evd);
   if (s != TG_OK) return s;
-  HIPCHK(hipEventRecord(b->ev1, st));
   b->launches++;
   b->inflight = true;
   b->last_stream = st;
@@ -3156,14 +3165,15 @@ tg_status tg_batch_wait(tg_batch b) {
   if (!b) return fail(TG_EINVAL, "batch is NULL");
   if (!b->inflight) return TG_OK;
   b->inflight = false;
-  HIPCHK(hipEventSynchronize(b->ev1));
+  HIPCHK(hipEventSynchronize(b->evd));
   return check_abort(b->lay.get());
 }
 
 tg_status tg_batch_time_ms(tg_batch b, double* ms) {
   if (!b || !ms) return fail(TG_EINVAL, "NULL argument");
   float f = 0;
-  HIPCHK(hipEventElapsedTime(&f, b->ev0, b->ev1));
+  // (before the first execution: events that were never recorded, an error)
+  HIPCHK(hipEventElapsedTime(&f, b->ev0, b->evd ? b->evd : b->rk1[0]));
   *ms = f;
   return TG_OK;
 }
@@ -3311,8 +3321,8 @@ tg_status tg_batch_autotune(tg_batch b, uint32_t reps, tg_exec_config* best, dou
 tg_status tg_batch_destroy(tg_batch b) {
   if (!b) return TG_OK;
   (void)tg_batch_wait(b);
+  b->lay.reset();  // leaves the ledger, whose entry holds one of the events below
   if (b->ev0) (void)hipEventDestroy(b->ev0);
-  if (b->ev1) (void)hipEventDestroy(b->ev1);
   for (uint32_t i = 0; i < tg_batch_s::kRing; ++i) {
     if (b->rk0[i]) (void)hipEventDestroy(b->rk0[i]);
     if (b->rk1[i]) (void)hipEventDestroy(b->rk1[i]);
@@ -3539,6 +3549,7 @@ tg_status tg_graph_execute_comparator(tg_graph g, uint32_t mode, void* stream) {
     HIPCHK(hipGraphLaunch(g->hgx, st));
   }
   HIPCHK(hipEventRecord(g->ev1, st));
+  g->evd = g->ev1;
   g->inflight = true;
   g->last_layout = nullptr;
   return TG_OK;
