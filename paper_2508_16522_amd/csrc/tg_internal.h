@@ -132,6 +132,7 @@ struct ExecParams {
   uint32_t* gdone;             // sinks finished per graph of the layout
   uint32_t* gflag;             // per graph, in host memory: gseq once it finished
   uint32_t gseq;
+  uint32_t* alarm;             // pinned host word, set when the abort flag is raised (or null)
   uint32_t gated;              // 1: a pre-condition wait precedes the launch; workers
                                // leave at once if it gave up (Ctrl::abort set)
   // diagnostics, last: the kernels read them rarely, and with these four
@@ -199,8 +200,8 @@ constexpr uint32_t kMaxGang = 32;  // workgroups per gang (mapping 3)
 hipError_t launch_reset(const ExecParams& p, hipStream_t s);
 // One wavefront waits until every pre-condition flag is met, for at most
 // timeout_ticks (s_memrealtime, 100 MHz); on time-out it raises ctrl->abort
-// and records the flag in ctrl->precond.
-hipError_t launch_wait_flags(const FlagWait& fw, Ctrl* ctrl, uint64_t timeout_ticks, hipStream_t s);
+// records the flag in ctrl->precond and sets *alarm (may be null).
+hipError_t launch_wait_flags(const FlagWait& fw, Ctrl* ctrl, uint32_t* alarm, uint64_t timeout_ticks, hipStream_t s);
 // Stores value into *flag (system scope, after a system-scope release) unless
 // ctrl->abort is set (the launch before it in stream order was abandoned).
 hipError_t launch_set_flag(uint32_t* flag, uint32_t value, const Ctrl* ctrl, hipStream_t s);

@@ -646,6 +646,12 @@ __device__ __forceinline__ uint32_t idle_step(const ExecParams& P, WorkerState& 
   return stalled(P, w.last, now) || (P.spin_limit != 0u && w.spins >= P.spin_limit) ? kStuck : kGoOn;
 }
 
+// Tells the host that the abort flag has been raised: it looks at the control
+// block only then.
+__device__ __forceinline__ void raise_alarm(uint32_t* alarm) {
+  if (alarm) __hip_atomic_store(alarm, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // A worker that found no progress raises the abort flag; the first one
 // records where it was stuck.
 __device__ __forceinline__ void report_stuck(const ExecParams& P, const WorkerState& w, uint32_t lane) {
@@ -658,6 +664,7 @@ __device__ __forceinline__ void report_stuck(const ExecParams& P, const WorkerSt
     st_coherent(&P.ctrl->stuck_h, w.h);
     st_coherent(&P.ctrl->stuck_wcnt, w.wcnt);
   }
+  raise_alarm(P.alarm);
 }
 
 // Diagnostics of one poll: first and last time, number.
@@ -975,6 +982,7 @@ __device__ void queue_abort(const ExecParams& P, const QueueState& q, uint32_t l
     st_coherent(&P.ctrl->stuck_h, q.shard);
     st_coherent(&P.ctrl->stuck_wcnt, P.npos);
   }
+  raise_alarm(P.alarm);
 }
 
 // The end of the launch: qsent exit sentinels into every shard.
@@ -1355,7 +1363,8 @@ __global__ __launch_bounds__(256) void k_build_records(const GraphSrc* gsrc, uin
 // Pre-condition vertices met by the host or by another launch (Section 4.1):
 // lane i polls flag i (system-scope loads of pinned host memory) until every
 // flag holds at least its value, or gives up after timeout_ticks.
-__global__ __launch_bounds__(64) void k_wait_flags(FlagWait fw, Ctrl* ctrl, uint64_t timeout_ticks) {
+__global__ __launch_bounds__(64) void k_wait_flags(FlagWait fw, Ctrl* ctrl, uint32_t* alarm,
+                                                   uint64_t timeout_ticks) {
   const uint32_t lane = threadIdx.x;
   const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
   for (;;) {
@@ -1367,6 +1376,7 @@ __global__ __launch_bounds__(64) void k_wait_flags(FlagWait fw, Ctrl* ctrl, uint
       if (lane == 0) {
         st_coherent(&ctrl->precond, 1u + (uint32_t)__builtin_ctzll(unmet));
         __hip_atomic_fetch_add(&ctrl->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        raise_alarm(alarm);
       }
       return;
     }
@@ -1411,9 +1421,9 @@ hipError_t launch_fill(uint32_t* p, uint64_t n, uint32_t v, hipStream_t s) {
 }
 
 
-hipError_t launch_wait_flags(const FlagWait& fw, Ctrl* ctrl, uint64_t timeout_ticks, hipStream_t s) {
+hipError_t launch_wait_flags(const FlagWait& fw, Ctrl* ctrl, uint32_t* alarm, uint64_t timeout_ticks, hipStream_t s) {
   if (fw.n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_wait_flags, dim3(1), dim3(64), 0, s, fw, ctrl, timeout_ticks);
+  hipLaunchKernelGGL(k_wait_flags, dim3(1), dim3(64), 0, s, fw, ctrl, alarm, timeout_ticks);
   return hipGetLastError();
 }
 
