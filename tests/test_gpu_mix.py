@@ -10,7 +10,7 @@ from tests.gpu_util import check_explicit, oracle_explicit, run
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rounds", [0, 1, 2, 63, 257])
+@pytest.mark.parametrize("rounds", [0, 1, 2, 7, 8, 9, 63, 257])
 @pytest.mark.parametrize("n", [64, 128, 256, 512])
 def test_mix_widths(gpu, n, rounds):
     # sources take every 32-bit pattern the hash gives; the second step mixes
