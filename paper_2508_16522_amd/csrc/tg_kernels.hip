@@ -266,6 +266,34 @@ __device__ __forceinline__ typename VecT<VEC>::T gather5(const ExecParams& P, co
   return ((p0 + p1) + (p2 + p3)) + p4;
 }
 
+// Issue priority of a wavefront (0 lowest).  A SIMD's wavefronts share its issue
+// slots by priority, not evenly: first the scheduling, payload and signal
+// phases and short mixes, which are a few instructions between memory round
+// trips and which other tasks wait for; then the mixes, those of the longer
+// tasks first, since a chain of them is what a launch of uneven graphs ends with;
+// last the polls of waiting workers.  48 graphs of log-normal costs over 4096
+// workers: 31.9 ms, with equal priorities 38.4 (with all three mix classes at one
+// priority 35.3, with polls at the highest 34.2); the 1024-column halo program on
+// gangs 16.1 ms, 16.7 before.  The thresholds are rounds times words per lane:
+// about 6 us and 90 us of a SIMD's time.
+constexpr uint32_t kPrioPoll = 0, kPrioShort = 3;
+
+// Around the mix of one chunk of a task of `len` words on S lanes.
+struct MixPriority {
+  uint32_t R, S;
+  uint64_t len;
+  __device__ __forceinline__ void operator()(bool begin) const {
+    if (!begin) {
+      __builtin_amdgcn_s_setprio(kPrioShort);
+    } else if (R >= 32u) {
+      const uint32_t w = min(R, 4095u) * (uint32_t)min(len, (uint64_t)0xFFFFFu);
+      if (w < S << 9) __builtin_amdgcn_s_setprio(0);
+      else if (w < S << 13) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(2);
+    }
+  }
+};
+
 // A task of NP predecessors whose payload takes several chunks, two chunks at
 // a time: the loads of both are in flight together, so a payload costs one
 // memory round trip per two chunks.  Up to three predecessors, whose two chunks
@@ -296,9 +324,9 @@ __device__ __forceinline__ uint32_t explicit_chunks(const Team& tm, const ExecPa
       q[0] += q[j];
     }
     const __amdgpu_buffer_rsrc_t wr = make_rsrc((const void*)r.out, nbytes);
-    const V x = mix_rounds(V(p[0] ^ r.tid), r.rounds);
+    const V x = mix_rounds(V(p[0] ^ r.tid), r.rounds, MixPriority{r.rounds, tm.ws(), n});
     buf_store<VEC>(x, wr, k0 * 4u);
-    const V y = mix_rounds(V(q[0] ^ r.tid), r.rounds);
+    const V y = mix_rounds(V(q[0] ^ r.tid), r.rounds, MixPriority{r.rounds, tm.ws(), n});
     buf_store<VEC>(y, wr, (k0 + step) * 4u);
     uint32_t dx = 0, dy = 0;
 #pragma unroll
@@ -330,7 +358,7 @@ __device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecPar
   uint32_t dsum = 0;
   if (n <= step && npred - 1u < 5u) {
     const uint32_t k0 = tm.wt() * VEC;
-    const V x = mix_rounds(V(gather5<VEC>(P, r, nbytes, k0, prefetch) ^ tid), R);
+    const V x = mix_rounds(V(gather5<VEC>(P, r, nbytes, k0, prefetch) ^ tid), R, MixPriority{R, S, n});
     buf_store<VEC>(x, wr, k0 * 4);
 #pragma unroll
     for (int i = 0; i < VEC; ++i) dsum += elem<VEC>(x, i) * (2u * (k0 + i) + 1u);
@@ -394,7 +422,7 @@ __device__ __forceinline__ uint32_t explicit_words(const Team& tm, const ExecPar
         }
       }
     }
-    const V x = mix_rounds(V(acc ^ tid), R);
+    const V x = mix_rounds(V(acc ^ tid), R, MixPriority{R, S, n});
     buf_store<VEC>(x, wr, k0 * 4);
     if (k0 < n) {
 #pragma unroll
@@ -457,7 +485,7 @@ __device__ __forceinline__ uint32_t body_implicit(const Team& tm, const ExecPara
     u32x4 x = load4(a, wt, S, len);
     for (uint64_t base = 0; base < len; base += step) {
       const u32x4 y = base + step < len ? load4(a + base + step, wt, S, len - base - step) : u32x4{0, 0, 0, 0};
-      x = mix_rounds(u32x4(x ^ key), R);
+      x = mix_rounds(u32x4(x ^ key), R, MixPriority{R, S, len});
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint64_t o = base + wt + (uint64_t)k * S;
@@ -639,6 +667,7 @@ __device__ __forceinline__ void idle_nap(const ExecParams& P, uint32_t spins) {
 // watchdog.
 __device__ __forceinline__ uint32_t idle_step(const ExecParams& P, WorkerState& w) {
   ++w.spins;
+  __builtin_amdgcn_s_setprio(kPrioPoll);
   idle_nap(P, w.spins);
   if ((w.spins & 63u) != 0u) return kGoOn;
   if (uni(ld_coherent(&P.ctrl->abort)) != 0u) return kLeave;
@@ -707,7 +736,8 @@ __device__ __forceinline__ uint32_t next_task(const ExecParams& P, WorkerState& 
     if (w.h >= w.wcnt) return kExit;
     w.pend = ready_scan<SCANREC>(lane, P, w, overlap);
     if (FULL) stamp_scan(P, w, lane);
-    while (!w.pend) {
+    if (w.pend) continue;
+    do {
       if (FULL && P.notify) {
         // wait for a message: one word per poll instead of the whole window
         // (a message rung before the last scan shows as a new value here, and
@@ -727,7 +757,8 @@ __device__ __forceinline__ uint32_t next_task(const ExecParams& P, WorkerState& 
       }
       w.pend = ready_scan<SCANREC>(lane, P, w, [] {});
       if (FULL) stamp_scan(P, w, lane);
-    }
+    } while (!w.pend);
+    __builtin_amdgcn_s_setprio(kPrioShort);
   }
 }
 
@@ -751,6 +782,7 @@ __device__ void residency_probe(const ExecParams& P, bool lead) {
 }
 
 __device__ __forceinline__ void worker_init(WorkerState& w, const ExecParams& P, uint32_t worker) {
+  __builtin_amdgcn_s_setprio(kPrioShort);
   w.worker = worker;
   w.wb = as_const(P.wbase)[worker];
   w.wcnt = as_const(P.wbase)[worker + 1] - w.wb;
@@ -960,6 +992,7 @@ __device__ __forceinline__ uint32_t* q_sinks(const ExecParams& P) { return P.qct
 
 // Workgroups are dealt to the 8 XCDs round-robin by workgroup index.
 __device__ __forceinline__ void queue_init(QueueState& q, const ExecParams& P, uint32_t worker) {
+  __builtin_amdgcn_s_setprio(kPrioShort);
   q.worker = worker;
   q.shard = blockIdx.x & 7u & (P.qshards - 1u);
   q.pshard = q.shard;
@@ -1049,6 +1082,7 @@ __device__ __forceinline__ uint32_t queue_next(const ExecParams& P, QueueState& 
     // loop a late claim delays a request (median latency 9.7 ms with the
     // fixed back-off, 11.4 ms with the growing one, same box).  Four naps (0.2
     // us) a poll: stencil 1024 x 500 1.76 ms, with one nap 1.80, with 16 1.83
+    __builtin_amdgcn_s_setprio(kPrioPoll);
     for (uint32_t spins = 1;; ++spins) {
       const uint32_t nap = spins < 64 ? 4u : max(P.idle_sleep, 4u);
       for (uint32_t i = 0; i < nap; ++i) __builtin_amdgcn_s_sleep(2);
@@ -1063,6 +1097,7 @@ __device__ __forceinline__ uint32_t queue_next(const ExecParams& P, QueueState& 
         }
       }
     }
+    __builtin_amdgcn_s_setprio(kPrioShort);
   }
   ++q.tile_i;
   if (v == kQExit) return kExit;

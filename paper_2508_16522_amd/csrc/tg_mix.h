@@ -86,40 +86,50 @@ __device__ __forceinline__ void mix_pair(uint32_t& x0, uint32_t& x1) {
 // everything waits for, pays for every taken branch: eight rounds a turn took
 // 1024 rounds of 4 words a lane from 58 to 48 us (the pure instruction time is
 // 41; four a turn: 50), and change nothing where the SIMD has other wavefronts to
-// issue from.  One test for tasks without rounds, which are a chain of memory
-// round trips.
-template <class Round>
-__device__ __forceinline__ void repeat_round(uint32_t R, Round&& round) {
-  if (R == 0) return;
+// issue from.  Tasks without rounds, which are a chain of memory round trips, fall
+// through one test (100 levels of butterfly 166 -> 162 us).
+template <class Round, class Around>
+__device__ __forceinline__ void repeat_round(uint32_t R, Round&& round, Around&& around) {
+  if (__builtin_expect(R == 0, 1)) return;
   constexpr uint32_t kTurn = 8;
+  around(true);
   for (; R >= kTurn; R -= kTurn) {
 #pragma unroll
     for (uint32_t i = 0; i < kTurn; ++i) round();
   }
   for (; R; --R) round();
+  around(false);
 }
 
-// R rounds on every word of x.
-__device__ __forceinline__ uint32_t mix_rounds(uint32_t x, uint32_t R) {
+// R rounds on every word of x.  around(true) runs before the first round,
+// around(false) after the last, neither if there are none.
+template <class Around>
+__device__ __forceinline__ uint32_t mix_rounds(uint32_t x, uint32_t R, Around&& around) {
   repeat_round(R, [&] {
     x ^= x << 13;
     x ^= x >> 17;
     x = xor_add(x, x << 5, kPre) * kMul;
-  });
+  }, around);
   return x;
 }
-__device__ __forceinline__ u32x2 mix_rounds(u32x2 v, uint32_t R) {
+template <class Around>
+__device__ __forceinline__ u32x2 mix_rounds(u32x2 v, uint32_t R, Around&& around) {
   uint32_t x0 = v[0], x1 = v[1];
-  repeat_round(R, [&] { mix_pair(x0, x1); });
+  repeat_round(R, [&] { mix_pair(x0, x1); }, around);
   return u32x2{x0, x1};
 }
-__device__ __forceinline__ u32x4 mix_rounds(u32x4 v, uint32_t R) {
+template <class Around>
+__device__ __forceinline__ u32x4 mix_rounds(u32x4 v, uint32_t R, Around&& around) {
   uint32_t x0 = v[0], x1 = v[1], x2 = v[2], x3 = v[3];
   repeat_round(R, [&] {
     mix_pair(x0, x1);
     mix_pair(x2, x3);
-  });
+  }, around);
   return u32x4{x0, x1, x2, x3};
+}
+template <class V>
+__device__ __forceinline__ V mix_rounds(V v, uint32_t R) {
+  return mix_rounds(v, R, [](bool) {});
 }
 
 }  // namespace tg
