@@ -615,6 +615,7 @@ struct HostLayout {
   std::vector<uint32_t> succ_pos;
   std::vector<uint32_t> indeg;
   std::vector<GraphEnt> gtab;
+  uint64_t data_words = 0;  // of the implicit graphs' shared arrays
   std::vector<std::vector<uint32_t>> pos_of;
 };
 
@@ -1120,7 +1121,12 @@ tg_status plan_layout(const std::vector<tg_graph>& gs, uint64_t nw_req, uint32_t
     for (auto& th : pool) th.join();
   }
   H.gtab.assign(gs.size(), GraphEnt());
-  for (uint32_t gi = 0; gi < gs.size(); ++gi) graph_entry(gs[gi], H.gtab[gi]);
+  H.data_words = 0;
+  for (uint32_t gi = 0; gi < gs.size(); ++gi) {
+    graph_entry(gs[gi], H.gtab[gi]);
+    H.gtab[gi].first = H.data_words;
+    if (gs[gi]->mode == TG_IMPLICIT) H.data_words += gs[gi]->space;
+  }
   return TG_OK;
 }
 
@@ -1289,6 +1295,8 @@ tg_status build_layout(const std::vector<tg_graph>& gs, const Config& cfg, std::
   P.cnt = L->cnt.as<uint32_t>();
   P.wbase = L->wbase.as<uint32_t>();
   P.gtab = L->gtab.as<GraphEnt>();
+  P.ngraphs = (uint32_t)gs.size();
+  P.data_words = H.data_words;
   P.ctrl = L->ctrl.as<tg::Ctrl>();
   P.owner = L->owner.as<uint32_t>();
   P.bell = L->bell.as<uint32_t>();
@@ -1425,10 +1433,12 @@ tg_status build_layout_device(const std::vector<tg_graph>& gs, const Config& cfg
   const uint32_t G = (uint32_t)gs.size();
   L.gtab_host.assign(G, GraphEnt());
   L.gsrc_host.assign(G, tg::GraphSrc());
-  uint64_t N = 0, Pn = 0, E = 0, nsrc = 0, nsinks = 0;
+  uint64_t N = 0, Pn = 0, E = 0, nsrc = 0, nsinks = 0, words = 0;
   for (uint32_t gi = 0; gi < G; ++gi) {
     const tg_graph g = gs[gi];
     graph_entry(g, L.gtab_host[gi]);
+    L.gtab_host[gi].first = words;
+    if (g->mode == TG_IMPLICIT) words += g->space;
     tg::GraphSrc& t = L.gsrc_host[gi];
     memset(&t, 0, sizeof(t));
     const uint32_t* b = L.blobs.as<uint32_t>() + boff[gi];
@@ -1521,6 +1531,8 @@ tg_status build_layout_device(const std::vector<tg_graph>& gs, const Config& cfg
   P.indeg = L.indeg.as<uint32_t>();
   P.cnt = L.cnt.as<uint32_t>();
   P.gtab = L.gtab.as<GraphEnt>();
+  P.ngraphs = (uint32_t)G;
+  P.data_words = words;
   P.ctrl = L.ctrl.as<tg::Ctrl>();
   P.bell = L.bell.as<uint32_t>();
   P.gang = 1;
@@ -2096,17 +2108,12 @@ tg_status launch_layout(Layout& L, const Config& cfg, const std::vector<tg_graph
     P.tstamp = L.tstamp.as<uint64_t>();
     P.wstamp = L.wstamp.as<uint64_t>();
   }
-  for (auto g : gs)
-    if (g->mode == TG_IMPLICIT) {
-      HIPCHK(tg_launch_init_data(g->data.as<uint32_t>(), g->space, sm64_host(g->seed ^ (2ull << 32)), st));
-    }
   const bool queue = L.cfg.dispatch == TG_DISPATCH_QUEUE;
   if (queue) {
     P.qtile = cfg.tile;
     P.qsent = cfg.tile * (L.qwmax + 1);
   }
   HIPCHK(tg::launch_reset(P, st));
-  if (queue) HIPCHK(tg::launch_queue_reset(P, st));
   P.gated = conds && conds->pre.n ? 1u : 0u;
   if (P.gated) HIPCHK(tg::launch_wait_flags(conds->pre, P.ctrl, P.alarm, P.watchdog_ticks, st));
   if (ring0) HIPCHK(hipEventRecord(ring0, st));

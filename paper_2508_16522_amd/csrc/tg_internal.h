@@ -24,6 +24,7 @@ struct GraphEnt {
   uint32_t mode;     // 1 explicit, 2 implicit
   uint32_t nsinks;   // tasks without out-edges (per-graph completion)
   uint32_t pad;
+  uint64_t first;    // words of the shared arrays of the graphs before this one
 };
 
 constexpr uint32_t kInPred = 6;  // predecessor payload addresses held in the record
@@ -100,6 +101,8 @@ struct ExecParams {
   uint32_t* cnt;               // pending in-edge counters
   const uint32_t* wbase;       // worker w owns positions [wbase[w], wbase[w+1])
   const GraphEnt* gtab;
+  uint32_t ngraphs;
+  uint64_t data_words;         // of the shared arrays of all graphs
   Ctrl* ctrl;
   const uint32_t* owner;       // worker of every position
   uint32_t* bell;              // per-worker doorbell, one per 128-byte line
@@ -120,7 +123,8 @@ struct ExecParams {
   uint32_t* q;                 // qshards x qcap ticket slots (kQEmpty when free)
   uint32_t* qctl;              // shard s: head at qctl[s * kQLine], tail at
                                // qctl[(qshards + s) * kQLine]; sinks finished
-                               // at qctl[2 * qshards * kQLine]
+                               // at qctl[2 * qshards * kQLine], and the blocks
+                               // of the reset that are done in the word after it
   const uint32_t* qsrc;        // positions without in-edges (pushed at reset)
   uint32_t nsrc;
   uint32_t nsinks;             // positions without out-edges
@@ -207,10 +211,7 @@ hipError_t launch_wait_flags(const FlagWait& fw, Ctrl* ctrl, uint32_t* alarm, ui
 hipError_t launch_set_flag(uint32_t* flag, uint32_t value, const Ctrl* ctrl, hipStream_t s);
 hipError_t launch_exec(const ExecParams& p, uint32_t mapping, uint32_t wg_waves, uint32_t grid_blocks,
                        hipStream_t s);
-// Ready-queue dispatch: clear the slots used by the previous launch, then
-// seed the queue with the sources (after launch_reset, before the executor).
-hipError_t launch_queue_reset(const ExecParams& p, hipStream_t s);
-// Only the clearing half: empties the slots the last launch of p filled.
+// Ready-queue dispatch: empties the slots the last launch of p filled.
 hipError_t launch_queue_clear(const ExecParams& p, hipStream_t s);
 hipError_t launch_exec_queue(const ExecParams& p, uint32_t mapping, uint32_t wg_waves, uint32_t grid_blocks,
                              hipStream_t s);

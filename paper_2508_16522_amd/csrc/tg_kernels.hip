@@ -189,7 +189,10 @@ __device__ __forceinline__ void unpack_rec(const Team& tm, const ExecParams& P, 
   r.shape = rl(r.v, kDwShape);
   r.digest = as_const(P.gtab)[r.graph].digest;
   r.succ0 = r.v;
-  if (r.nsucc > kInSucc && tm.t >= kInSucc && tm.t < r.nsucc) r.succ0 = P.succ_pos[r.succ_beg + tm.t];
+  if (r.nsucc > kInSucc) {
+    const uint32_t s = P.succ_pos[r.succ_beg + min(tm.t, r.nsucc - 1u)];
+    if (tm.t >= kInSucc) r.succ0 = s;
+  }
 }
 
 // Payload address of predecessor j (j wave-uniform).
@@ -1241,8 +1244,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   if (wave == 0 && q.stop == kStuck) queue_abort(P, q, lane, q.stuck);
 }
 
-// Empties the slots the previous launch filled: [0, tail) of every shard
-// (the tails are still the previous launch's; k_queue_seed resets them).
+// Empties the slots the previous launch filled: [0, tail) of every shard.
 __global__ __launch_bounds__(256) void k_queue_clear(ExecParams P) {
   const uint32_t stride = gridDim.x * blockDim.x;
   for (uint32_t s = 0; s < P.qshards; ++s) {
@@ -1250,19 +1252,6 @@ __global__ __launch_bounds__(256) void k_queue_clear(ExecParams P) {
     if (t > P.qcap) t = P.qcap;
     for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < t; i += stride) P.q[(size_t)s * P.qcap + i] = kQEmpty;
   }
-}
-
-// Sources dealt round-robin over the shards; heads, tails and the sink count
-// reset.
-__global__ __launch_bounds__(256) void k_queue_seed(ExecParams P) {
-  const uint32_t stride = gridDim.x * blockDim.x;
-  const uint32_t gid = blockIdx.x * blockDim.x + threadIdx.x;
-  for (uint32_t i = gid; i < P.nsrc; i += stride) P.q[(size_t)(i % P.qshards) * P.qcap + i / P.qshards] = P.qsrc[i];
-  if (gid < P.qshards) {
-    *q_head(P, gid) = 0u;
-    *q_tail(P, gid) = (P.nsrc + P.qshards - 1u - gid) / P.qshards;
-  }
-  if (gid == 0) *q_sinks(P) = 0u;
 }
 
 // Residency probes: the executors' launch bounds and occupancy attributes
@@ -1282,11 +1271,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   __syncthreads();
 }
 
+// Everything a launch starts from, in one kernel (a launch of its own costs
+// about 10 us before the executor can start): counters, diagnostics, the shared
+// arrays of implicit graphs, and the queue.
 __global__ __launch_bounds__(256) void k_reset(ExecParams P) {
   const uint32_t stride = gridDim.x * blockDim.x;
   for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < P.npos; i += stride) {
     P.cnt[i] = P.indeg[i];
     if (P.execs) P.execs[i] = 0;
+  }
+  for (uint64_t i = blockIdx.x * blockDim.x + threadIdx.x; i < P.data_words; i += stride) {
+    uint32_t lo = 0, hi = P.ngraphs;  // the last graph whose words begin at or before i
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (P.gtab[mid].first <= i) lo = mid;
+      else hi = mid;
+    }
+    const GraphEnt& g = P.gtab[lo];
+    g.data[i - g.first] = h32k(g.key2, i - g.first);
   }
   // gangs add their members' digest parts into the digest words
   if (P.gang > 1)
@@ -1310,6 +1312,27 @@ __global__ __launch_bounds__(256) void k_reset(ExecParams P) {
     P.ctrl->progress = 0;
     P.ctrl->precond = 0;
   }
+  if (!P.q) return;
+  // queue: the sources dealt round-robin over the shards, and the rest of the
+  // slots the previous launch filled emptied (the tails are still that
+  // launch's); the last block to get there resets the heads, the tails and the
+  // sink count, which every block has read by then
+  const uint32_t S = P.qshards;
+  for (uint32_t s = 0; s < S; ++s) {
+    const uint32_t mine = (P.nsrc + S - 1u - s) / S, used = max(mine, min(*q_tail(P, s), P.qcap));
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < used; i += stride)
+      P.q[(size_t)s * P.qcap + i] = i < mine ? P.qsrc[i * S + s] : kQEmpty;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  const uint32_t before = __hip_atomic_fetch_add(q_sinks(P) + 1, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+  if (before + 1u != gridDim.x) return;
+  for (uint32_t s = 0; s < S; ++s) {
+    *q_head(P, s) = 0u;
+    *q_tail(P, s) = (P.nsrc + S - 1u - s) / S;
+  }
+  q_sinks(P)[0] = 0u;
+  q_sinks(P)[1] = 0u;
 }
 
 // Comparator: one launch runs one task; ordering comes from the stream or
@@ -1467,11 +1490,11 @@ hipError_t launch_set_flag(uint32_t* flag, uint32_t value, const Ctrl* ctrl, hip
   return hipGetLastError();
 }
 
+// A queue's blocks take a ticket each, so there are fewer of them.
 hipError_t launch_reset(const ExecParams& p, hipStream_t s) {
-  uint32_t blocks = (p.npos + 255u) / 256u;
-  if (blocks > 4096u) blocks = 4096u;
-  if (blocks == 0) blocks = 1;
-  hipLaunchKernelGGL(k_reset, dim3(blocks), dim3(256), 0, s, p);
+  const uint64_t blocks = (std::max<uint64_t>(p.npos, p.data_words) + 255u) / 256u;
+  const uint64_t most = p.q ? 1024u : 4096u;
+  hipLaunchKernelGGL(k_reset, dim3((uint32_t)std::max<uint64_t>(1u, std::min(blocks, most))), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -1501,20 +1524,6 @@ hipError_t launch_queue_clear(const ExecParams& p, hipStream_t s) {
   if (blocks > 4096u) blocks = 4096u;
   if (blocks == 0) blocks = 1;
   hipLaunchKernelGGL(k_queue_clear, dim3(blocks), dim3(256), 0, s, p);
-  return hipGetLastError();
-}
-
-hipError_t launch_queue_reset(const ExecParams& p, hipStream_t s) {
-  uint32_t blocks = (p.npos + 255u) / 256u;
-  if (blocks > 4096u) blocks = 4096u;
-  if (blocks == 0) blocks = 1;
-  hipLaunchKernelGGL(k_queue_clear, dim3(blocks), dim3(256), 0, s, p);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  uint32_t sb = (p.nsrc + 255u) / 256u;
-  if (sb > 4096u) sb = 4096u;
-  if (sb == 0) sb = 1;
-  hipLaunchKernelGGL(k_queue_seed, dim3(sb), dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
