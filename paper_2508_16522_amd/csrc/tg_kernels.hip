@@ -281,7 +281,8 @@ __device__ __forceinline__ typename VecT<VEC>::T gather5(const ExecParams& P, co
 // about 6 us and 90 us of a SIMD's time.
 constexpr uint32_t kPrioPoll = 0, kPrioShort = 3;
 
-// Around the mix of one chunk of a task of `len` words on S lanes.
+// Around the mix of a task of `len` words on S lanes (of one chunk, or of all: once
+// a chunk cost a 64 KiB stencil 3% of its time and halo tasks 1%).
 struct MixPriority {
   uint32_t R, S;
   uint64_t len;
@@ -312,6 +313,8 @@ __device__ __forceinline__ uint32_t explicit_chunks(const Team& tm, const ExecPa
   const uint32_t nbytes = n * 4u, step = VEC * tm.ws();
   const uint32_t pairs = uni((n + 2u * step - 1u) / (2u * step));
   uint32_t k0 = tm.wt() * VEC, dsum = 0;
+  const MixPriority prio{r.rounds, tm.ws(), n};
+  prio(true);
   for (uint32_t c = 0; c < pairs; ++c) {
     V p[NP], q[NP];
 #pragma unroll
@@ -327,9 +330,9 @@ __device__ __forceinline__ uint32_t explicit_chunks(const Team& tm, const ExecPa
       q[0] += q[j];
     }
     const __amdgpu_buffer_rsrc_t wr = make_rsrc((const void*)r.out, nbytes);
-    const V x = mix_rounds(V(p[0] ^ r.tid), r.rounds, MixPriority{r.rounds, tm.ws(), n});
+    const V x = mix_rounds(V(p[0] ^ r.tid), r.rounds);
     buf_store<VEC>(x, wr, k0 * 4u);
-    const V y = mix_rounds(V(q[0] ^ r.tid), r.rounds, MixPriority{r.rounds, tm.ws(), n});
+    const V y = mix_rounds(V(q[0] ^ r.tid), r.rounds);
     buf_store<VEC>(y, wr, (k0 + step) * 4u);
     uint32_t dx = 0, dy = 0;
 #pragma unroll
@@ -340,6 +343,7 @@ __device__ __forceinline__ uint32_t explicit_chunks(const Team& tm, const ExecPa
     dsum += (k0 < n ? dx : 0u) + (k0 + step < n ? dy : 0u);
     k0 += 2u * step;
   }
+  prio(false);
   return dsum;
 }
 
@@ -486,9 +490,11 @@ __device__ __forceinline__ uint32_t body_implicit(const Team& tm, const ExecPara
     // next chunk's loads are issued before this chunk's mix
     const uint64_t step = 4 * (uint64_t)S;
     u32x4 x = load4(a, wt, S, len);
+    const MixPriority prio{R, S, len};
+    prio(true);
     for (uint64_t base = 0; base < len; base += step) {
       const u32x4 y = base + step < len ? load4(a + base + step, wt, S, len - base - step) : u32x4{0, 0, 0, 0};
-      x = mix_rounds(u32x4(x ^ key), R, MixPriority{R, S, len});
+      x = mix_rounds(u32x4(x ^ key), R);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
         const uint64_t o = base + wt + (uint64_t)k * S;
@@ -499,6 +505,7 @@ __device__ __forceinline__ uint32_t body_implicit(const Team& tm, const ExecPara
       }
       x = y;
     }
+    prio(false);
   }
   return dsum;
 }
