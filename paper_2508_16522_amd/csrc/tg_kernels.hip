@@ -120,27 +120,38 @@ struct WaveTeam {
   __device__ __forceinline__ uint32_t wt() const { return t; }
   __device__ __forceinline__ uint32_t ws() const { return 64; }
   __device__ __forceinline__ uint32_t sum(uint32_t v) const { return wave_sum(v); }
+  __device__ __forceinline__ uint32_t digest_sum(uint32_t v) const { return wave_sum(v); }
   __device__ __forceinline__ void sync() const {}
   __device__ __forceinline__ bool leader() const { return t == 0; }
 };
 
 struct BlockTeam {
   uint32_t t, n;
-  uint32_t* lds;  // >= 17 words
+  uint32_t* lds;  // 32 words: partial sums of sum() and, from 16, of the digest
   __device__ __forceinline__ uint32_t size() const { return n; }
   __device__ __forceinline__ uint32_t wt() const { return t; }
   __device__ __forceinline__ uint32_t ws() const { return n; }
   __device__ __forceinline__ void sync() const { __syncthreads(); }
   __device__ __forceinline__ bool leader() const { return t == 0; }
+  // At most once a task: the barrier before the edge signals (complete_edges)
+  // stands between the reads of one task's sum and the writes of the next one's.
   __device__ uint32_t sum(uint32_t v) const {
+    put_sum(v, 0);
+    __syncthreads();
+    return get_sum(0);
+  }
+  __device__ uint32_t digest_sum(uint32_t v) const {
+    put_sum(v, 16);
+    __syncthreads();
+    return get_sum(16);
+  }
+  __device__ __forceinline__ void put_sum(uint32_t v, uint32_t at) const {
     v = wave_sum(v);
-    const uint32_t w = t >> 6;
-    __syncthreads();
-    if ((t & 63) == 0) lds[w] = v;
-    __syncthreads();
-    uint32_t s = 0;
-    for (uint32_t i = 0; i < (n >> 6); ++i) s += lds[i];
-    return s;
+    if ((t & 63) == 0) lds[at + (t >> 6)] = v;
+  }
+  __device__ __forceinline__ uint32_t get_sum(uint32_t at) const {
+    const uint32_t i = t & 63u;
+    return wave_sum(i < (n >> 6) ? lds[at + i] : 0u);
   }
 };
 
@@ -527,7 +538,7 @@ __device__ __forceinline__ uint32_t run_body(const Team& tm, const ExecParams& P
 // is in memory once the leader's stores are drained.
 template <class Team>
 __device__ __forceinline__ void store_digest(const Team& tm, const Rec& r, uint32_t part) {
-  const uint32_t d = tm.sum(part);
+  const uint32_t d = tm.digest_sum(part);
   if (tm.leader()) st_coherent(r.digest + r.tid, d);
 }
 
@@ -861,6 +872,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 // One workgroup per task: wave 0 runs the scheduling state machine and
 // stages the chosen position and its record in LDS; every wave then executes
 // the same sequence of barriers for each task.
+// Two barriers a task: A, behind which the task is known, and B, behind which all
+// payload stores are drained (complete_edges; a task with read-only elements has
+// one more in their sum, whose words no other sum uses).  The position and record are written
+// before A and read before B, so the next ones need no barrier of their own; the
+// digest's partial sums are written after B and added up behind the next A.
+// Five barriers a task before: 64 KiB stencil 447 -> 432 us, 128 x 40 butterfly of
+// 64 KiB 243 -> 237 us, 1024-column halo on gangs 15.8 -> 15.6 ms.
 template <bool FULL>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) void k_exec_block(ExecParams P) {
   __shared__ uint32_t lds[32];
@@ -874,7 +892,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     __hip_atomic_fetch_add(&P.ctrl->started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   WorkerState w;
   worker_init(w, P, worker);
+  uint32_t part = 0;            // digest part of the last task: summed over the barrier
+  uint32_t* part_of = nullptr;  // behind which the next task is known, and stored here
   for (;;) {
+    if (part_of) tm.put_sum(part, 16);
     if (wave == 0) {
       const uint32_t pos = next_task<FULL, true>(P, w, lane, [] {});
       if (pos != kExit) {
@@ -886,15 +907,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     __syncthreads();
     const uint32_t pos = uni(cmd);
     const uint32_t v = recl[lane & 31u];
-    __syncthreads();
+    if (part_of && wave == 0) {
+      const uint32_t d = tm.get_sum(16);
+      if (lane == 0) st_coherent(part_of, d);
+    }
     if (pos == kExit) break;
     Rec r;
     unpack_rec(tm, P, v, r);
-    const uint32_t part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
+    part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
     complete_edges<FULL>(tm, P, r);
-    store_digest(tm, r, part);
+    part_of = r.digest + r.tid;
     if (FULL && P.tstamp && threadIdx.x == 0) P.tstamp[2 * pos + 1] = __builtin_amdgcn_s_memrealtime();
-    __syncthreads();
   }
   if (wave == 0) report_stuck(P, w, lane);
   if (FULL && P.wprog && threadIdx.x == 0) P.wprog[worker] = w.h;
@@ -927,7 +950,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
   const uint32_t lane = threadIdx.x & 63u, wave = uni(threadIdx.x >> 6);
   WorkerState w;
   worker_init(w, P, gang);
+  uint32_t part = 0;            // digest part of the last task: summed over the barrier
+  uint32_t* part_of = nullptr;  // behind which the next task is known, and stored here
   for (;;) {
+    if (part_of) tm.put_sum(part, 16);
     if (wave == 0) {
       const uint32_t pos = next_task<FULL, true>(P, w, lane, [] {});
       if (pos != kExit) {
@@ -939,20 +965,20 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8))) vo
     __syncthreads();
     const uint32_t pos = uni(cmd);
     const uint32_t v = recl[lane & 31u];
-    __syncthreads();
+    if (part_of && wave == 0) {
+      const uint32_t d = tm.get_sum(16);
+      if (lane == 0) __hip_atomic_fetch_add(part_of, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (pos == kExit) break;
     Rec r;
     unpack_rec(tm, P, v, r);
-    const uint32_t part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
+    part = run_body<FULL>(tm, P, pos, r, NoPrefetch());
     complete_edges<FULL>(tm, P, r);
-    const uint32_t d = tm.sum(part);
-    if (threadIdx.x == 0)
-      __hip_atomic_fetch_add(r.digest + r.tid, d, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    part_of = r.digest + r.tid;
     // diagnostics: a task ends when its last member finishes
     if (FULL && P.tstamp && threadIdx.x == 0)
       __hip_atomic_fetch_max(P.tstamp + 2 * pos + 1, __builtin_amdgcn_s_memrealtime(), __ATOMIC_RELAXED,
                              __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();
   }
   if (wave == 0) report_stuck(P, w, lane);
   if (FULL && member == 0 && P.wprog && threadIdx.x == 0) P.wprog[gang] = w.h;
