@@ -2635,9 +2635,9 @@ static tg_status graph_execute(tg_graph g, const tg_exec_config* cfgp, void* str
   // level order over all resident workers puts a task and its successor of the
   // same lane on different ones as soon as the level's width does not divide
   // their number, so every edge is a hand-off and thousands of workers poll.
-  // Measured (kernel, level / column, us): butterfly 300 x 100 271 / 164, random
-  // 1024 x 50 217 / 116, stencil 8 x 16 41 / 40, tree 1024 x 60 with 1024 rounds
-  // 5264 / 3824, halo 32 x 32 687 / 601, no dependences 1024 x 500 320 / 321.
+  // Measured (kernel, level / column, us): butterfly 300 x 100 265 / 164, random
+  // 1024 x 50 210 / 116, stencil 8 x 16 39 / 37, tree 1024 x 60 with 1024 rounds
+  // 3530 / 2880, halo 32 x 32 624 / 542, no dependences 1024 x 500 315 / 317.
   // Gangs keep level order, the queue has no lists, and a batch of
   // graphs of different widths and costs has no columns to keep.
   if ((!given || (!given->schedule && !given->workers)) && cfg.dispatch == TG_DISPATCH_LISTS && cfg.mapping != TG_MAP_GANG)

@@ -288,8 +288,8 @@ __device__ __forceinline__ typename VecT<VEC>::T gather5(const ExecParams& P, co
 // last the polls of waiting workers.  48 graphs of log-normal costs over 4096
 // workers: 31.9 ms, with equal priorities 38.4 (with all three mix classes at one
 // priority 35.3, with polls at the highest 34.2); the 1024-column halo program on
-// gangs 16.1 ms, 16.7 before.  The thresholds are rounds times words per lane:
-// about 6 us and 90 us of a SIMD's time.
+// gangs 16.1 ms, 16.7 with equal ones.  The thresholds are rounds times words per lane:
+// about 5 us and 80 us of a SIMD's time.
 constexpr uint32_t kPrioPoll = 0, kPrioShort = 3;
 
 // Around the mix of a task of `len` words on S lanes (of one chunk, or of all: once
@@ -313,8 +313,9 @@ struct MixPriority {
 // a time: the loads of both are in flight together, so a payload costs one
 // memory round trip per two chunks.  Up to three predecessors, whose two chunks
 // take 24 vector registers; four or five would spill.  192 x 40 stencil tasks of
-// 64 KiB (about 0.2 ms of traffic) take 415 us on four wavefronts each, 749 us
-// one chunk at a time; 512 x 200 of 4 KiB on one wavefront 543 and 975 us.
+// 64 KiB (about 0.2 ms of traffic) took 415 us on four wavefronts each, 749 us
+// one chunk at a time, and 512 x 200 of 4 KiB on one wavefront 543 and 975 us
+// (432 and 543 us since the mix is unrolled and the barriers are two).
 // Issuing the next pair's loads before this pair's mix as well spills too: 367
 // us for the former, 635 us for the latter.
 template <int VEC, int NP, class Team, class Prefetch>
