@@ -284,6 +284,11 @@ int StageUse::made = 0;
 // through the legacy null stream and have ended on return.
 hipError_t copy_out(void* host, const void* devp, size_t bytes) {
   if (bytes == 0) return hipSuccess;
+  // memory the runtime knows (pinned, managed, on a device) needs no stage
+  hipPointerAttribute_t known;
+  if (hipPointerGetAttributes(&known, host) == hipSuccess && known.type != hipMemoryTypeUnregistered)
+    return hipMemcpy(host, devp, bytes, hipMemcpyDeviceToHost);
+  (void)hipGetLastError();  // an ordinary address may be reported as an error
   std::atomic<size_t> next{0};
   std::atomic<int> err{(int)hipSuccess};
   const size_t blocks = (bytes + StageUse::kBytes - 1) / StageUse::kBytes;

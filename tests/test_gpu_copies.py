@@ -26,6 +26,7 @@ def one_sweep(words):
 
 @pytest.mark.parametrize("words", [MIB - 1, MIB, MIB + 1, 2 * MIB + 1, 3 * MIB, 17 * MIB + 3])
 def test_blocks(gpu, words):
+    import torch
     ig = one_sweep(words)
     ref = oracle.implicit_program_order(ig.N, ig.req_ptr, ig.lo, ig.hi, ig.priv, ig.rounds, ig.space, seed=ig.seed)["A"]
     g = tg.graph_from_implicit(ig)
@@ -37,5 +38,8 @@ def test_blocks(gpu, words):
     assert part(0, words)
     assert part(words - 1, words) and part(words, words)
     assert part(7, words - 5)
+    pinned = torch.zeros(words, dtype=torch.int32, pin_memory=True)  # copied to directly
+    tg._check(tg.load().tg_graph_read_data(g.handle, pinned.data_ptr(), 0, words), "tg_graph_read_data")
+    assert np.array_equal(pinned.numpy().view(np.uint32), ref)
     with ThreadPoolExecutor(12) as ex:
         assert all(ex.map(lambda k: part(k, words - k), range(12)))
