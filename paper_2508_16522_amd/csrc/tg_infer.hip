@@ -1218,26 +1218,27 @@ tg_status infer_entries(Workspace& ws, uint32_t N, uint64_t space, const tg_regi
 //                         buffer of the exact size is taken from the
 //                         workspace, else *col (capacity col_cap) is used
 //                         and a larger edge count fails with TG_ENOMEM;
-//   *E                  : the edge count (set also on TG_ENOMEM).
+//   *E                  : the edge count (set also on TG_ENOMEM);
+//   pin                 : pinned words for the small results, or null.
 // Returns when the DAG is complete on the device.
-tg_status infer_core(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, const tg_region_req* rq,
-                     const uint64_t* req_ptr, uint64_t max_buckets, hipStream_t st, uint64_t* row, uint32_t** col, bool alloc_col, uint64_t col_cap, uint64_t* E) {
+tg_status infer_steps(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, const tg_region_req* rq,
+                      const uint64_t* req_ptr, uint64_t max_buckets, hipStream_t st, uint64_t* pin, uint64_t* row,
+                      uint32_t** col, bool alloc_col, uint64_t col_cap, uint64_t* E) {
   hipError_t e;
   *E = 0;
   if (M >= 0xFFFFFFFFull) return tg_set_error(TG_EINVAL, "too many region requirements");
   const uint32_t M32 = (uint32_t)M;
-  const PinBlock pb;
   const size_t used0 = ws.used;
   unsigned long long* summary = nullptr;
   ICHK(ws.get(tg::kSumAlloc * 8, "summary", (void**)&summary), "summary");
   ICHK(tg::fill_u32((uint32_t*)summary, tg::kSumAlloc * 2, 0, st), "clear");
   hipLaunchKernelGGL(tg::k_check_reqs, dim3(big_blocks(N)), dim3(tg::kTaskThreads), 0, st, rq, req_ptr, N, M,
-                     space, summary, pb.p);
+                     space, summary, pin);
   ICHK(hipGetLastError(), "k_check_reqs");
   uint64_t sum[tg::kSumWords];
-  if (pb.p) {
+  if (pin) {
     ICHK(hipStreamSynchronize(st), "requirement check");
-    for (uint32_t i = 0; i < tg::kSumWords; ++i) sum[i] = __atomic_load_n(pb.p + i, __ATOMIC_ACQUIRE);
+    for (uint32_t i = 0; i < tg::kSumWords; ++i) sum[i] = __atomic_load_n(pin + i, __ATOMIC_ACQUIRE);
   } else {
     ICHK(read_back(sum, summary, sizeof(sum), st), "summary read-back");
   }
@@ -1269,7 +1270,7 @@ tg_status infer_core(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, cons
     // 32-bit offsets inside a bucket, and 32-bit entry indices
     if (es <= 31 && bound < 4.0e9L) {
       bool done = false;
-      const tg_status s = infer_entries(ws, N, space, rq, req_ptr, es, (uint64_t)bound + 1, st, pb.p, row, col, alloc_col,
+      const tg_status s = infer_entries(ws, N, space, rq, req_ptr, es, (uint64_t)bound + 1, st, pin, row, col, alloc_col,
                                         col_cap, E, &done);
       if (s != TG_OK || done) return s;
     }
@@ -1322,6 +1323,18 @@ tg_status infer_core(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, cons
   }
   ICHK(hipStreamSynchronize(st), "inference");
   return TG_OK;
+}
+
+// infer_steps with what it shares given back safely: on an error kernels may
+// still be queued that store into the pinned words, or into a scratch array the
+// caller is about to release, so the stream is waited for first.
+tg_status infer_core(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, const tg_region_req* rq,
+                     const uint64_t* req_ptr, uint64_t max_buckets, hipStream_t st, uint64_t* row, uint32_t** col,
+                     bool alloc_col, uint64_t col_cap, uint64_t* E) {
+  const PinBlock pb;
+  const tg_status s = infer_steps(ws, N, M, space, rq, req_ptr, max_buckets, st, pb.p, row, col, alloc_col, col_cap, E);
+  if (s != TG_OK) (void)hipStreamSynchronize(st);
+  return s;
 }
 
 #undef ICHK
