@@ -1037,38 +1037,47 @@ class SpareUse {
 
 // Pinned host words that kernels store small results into (a copy engine's
 // read-back costs about 10 us more).  One block per inference in flight, kept
-// for the next; a process holds as many as it ever ran at once.  Without pinned
-// memory the results are copied back instead.
+// for the next; a process holds as many as its allocating inferences ever ran at
+// once.  An allocation-free call (make = false) uses a block that one of those
+// left and makes none.  Without a block the results are copied back instead.
 struct PinBlock {
   static constexpr size_t kWords = 128;  // the summary, then the edge and entry counts
   uint64_t* p = nullptr;
-  PinBlock() {
-    std::lock_guard<std::mutex> lk(mu());
-    if (!list().empty()) {
-      p = list().back();
-      list().pop_back();
+  explicit PinBlock(bool make) {
+    Pool& pl = pool();
+    std::lock_guard<std::mutex> lk(pl.mu);
+    if (!pl.free.empty()) {
+      p = pl.free.back();
+      pl.free.pop_back();
       return;
     }
+    if (!make) return;
+    pl.free.reserve(pl.made + 1);  // giving a block back never allocates
     void* v = nullptr;
-    if (hipHostMalloc(&v, kWords * 8, hipHostMallocCoherent | hipHostMallocMapped) == hipSuccess) p = (uint64_t*)v;
-    else (void)hipGetLastError();
+    if (hipHostMalloc(&v, kWords * 8, hipHostMallocCoherent | hipHostMallocMapped) == hipSuccess) {
+      p = (uint64_t*)v;
+      ++pl.made;
+    } else {
+      (void)hipGetLastError();
+    }
   }
   ~PinBlock() {
     if (!p) return;
-    std::lock_guard<std::mutex> lk(mu());
-    list().push_back(p);
+    std::lock_guard<std::mutex> lk(pool().mu);
+    pool().free.push_back(p);
   }
   PinBlock(const PinBlock&) = delete;
   PinBlock& operator=(const PinBlock&) = delete;
 
  private:
-  static std::mutex& mu() {
-    static std::mutex* m = new std::mutex;
-    return *m;
-  }
-  static std::vector<uint64_t*>& list() {
-    static std::vector<uint64_t*>* l = new std::vector<uint64_t*>;
-    return *l;
+  struct Pool {
+    std::mutex mu;
+    std::vector<uint64_t*> free;
+    size_t made = 0;
+  };
+  static Pool& pool() {
+    static Pool* pl = new Pool;
+    return *pl;
   }
 };
 
@@ -1331,7 +1340,7 @@ tg_status infer_steps(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, con
 tg_status infer_core(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, const tg_region_req* rq,
                      const uint64_t* req_ptr, uint64_t max_buckets, hipStream_t st, uint64_t* row, uint32_t** col,
                      bool alloc_col, uint64_t col_cap, uint64_t* E) {
-  const PinBlock pb;
+  const PinBlock pb(ws.spill);  // a workspace that may not allocate: no block made either
   const tg_status s = infer_steps(ws, N, M, space, rq, req_ptr, max_buckets, st, pb.p, row, col, alloc_col, col_cap, E);
   if (s != TG_OK) (void)hipStreamSynchronize(st);
   return s;
