@@ -1054,7 +1054,8 @@ struct PinBlock {
     if (!make) return;
     pl.free.reserve(pl.made + 1);  // giving a block back never allocates
     void* v = nullptr;
-    if (hipHostMalloc(&v, kWords * 8, hipHostMallocCoherent | hipHostMallocMapped) == hipSuccess) {
+    // portable: the pool serves every device
+    if (hipHostMalloc(&v, kWords * 8, hipHostMallocCoherent | hipHostMallocMapped | hipHostMallocPortable) == hipSuccess) {
       p = (uint64_t*)v;
       ++pl.made;
     } else {

@@ -57,7 +57,7 @@ same(infer_on_device(small, fn=free), small)
 same(infer_on_device(small, fn=free), small)
 same(infer_on_device(small, fn=alloc), small)
 same(infer_on_device(small, fn=free), small)
-assert alloc_calls[0] > 0, "the shim saw nothing"
 assert free_calls == [0, 0, 0], free_calls
+assert alloc_calls[0] > 0, "the shim saw nothing"
 print("done")
 """)

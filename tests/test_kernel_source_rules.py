@@ -93,3 +93,13 @@ def test_edge_signals_follow_the_drain():
         assert "vm_drain()" in body, k
         first_signal = min(i for i in (body.find("signal_edge"), body.find("__hip_atomic_fetch")) if i >= 0)
         assert body.find("vm_drain()") < first_signal, k
+
+
+def test_pinned_pools_serve_every_device():
+    # pools of pinned words that are shared by all devices of a process
+    for name, pools in (("tg_host.cpp", ("class AlarmWord", "struct StageUse")), ("tg_infer.hip", ("struct PinBlock",))):
+        src = open(os.path.join(os.path.dirname(SRC), name)).read()
+        for pool in pools:
+            body = src[src.index(pool + " {"):]
+            calls = re.findall(r"hipHostMalloc\(([^;{]*)", body[:body.index("\n};")])
+            assert calls and all("hipHostMallocPortable" in c for c in calls), pool
