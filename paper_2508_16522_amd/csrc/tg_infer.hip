@@ -772,6 +772,13 @@ struct Workspace {
     if (e == hipSuccess) owned.push_back(*out);
     return e;
   }
+  // Gives back what was taken since the region was at `used0` with `owned0`
+  // allocations; the device must have finished with it.
+  void rewind(size_t used0, size_t owned0) {
+    used = used0;
+    missing = nullptr;
+    for (; owned.size() > owned0; owned.pop_back()) (void)hipFree(owned.back());
+  }
 };
 
 __global__ void k_fill_u32(uint32_t* p, uint64_t n, uint32_t v) {
@@ -1109,14 +1116,21 @@ uint32_t entry_shift(const uint64_t* cls, uint64_t space, uint64_t max_buckets) 
     }                                                                                                   \
   } while (0)
 
-// The edge buffer of a counted DAG (E edges), as infer_core's contract.
-tg_status edge_buffer(Workspace& ws, uint64_t E, uint32_t** col, bool alloc_col, uint64_t col_cap) {
-  hipError_t e;
+// Whether a DAG of E edges can be returned (a caller's buffer holds col_cap).
+tg_status edge_count_ok(uint64_t E, bool alloc_col, uint64_t col_cap) {
   if (E >= 0xFFFFFFFFull) return tg_set_error(TG_EINVAL, "inferred DAG has too many edges (%llu)", (unsigned long long)E);
-  if (alloc_col) ICHK(ws.get(E * 4, "edges", (void**)col), "edge array");
-  else if (E > col_cap)
+  if (!alloc_col && E > col_cap)
     return tg_set_error(TG_ENOMEM, "inferred DAG has %llu edges, capacity %llu", (unsigned long long)E,
                         (unsigned long long)col_cap);
+  return TG_OK;
+}
+
+// The edge buffer of a counted DAG (E edges), as infer_steps' contract.
+tg_status edge_buffer(Workspace& ws, uint64_t E, uint32_t** col, bool alloc_col, uint64_t col_cap) {
+  hipError_t e;
+  const tg_status s = edge_count_ok(E, alloc_col, col_cap);
+  if (s != TG_OK) return s;
+  if (alloc_col) ICHK(ws.get(E * 4, "edges", (void**)col), "edge array");
   return TG_OK;
 }
 
@@ -1130,26 +1144,36 @@ uint32_t big_blocks(uint32_t N) {
   return (uint32_t)std::min<uint64_t>(((uint64_t)N * tg::kSub + tg::kTaskThreads - 1) / tg::kTaskThreads, 256);
 }
 
-// Rows from sorted entries.  *done = false (and nothing touched but scratch
-// memory) if the entries do not fit the workspace's fixed region.
+// Rows from sorted entries.  *done = false (and nothing but scratch memory and
+// row touched) if the entries do not fit the workspace's fixed region or, where it
+// may allocate, the device's memory: the other pipeline takes a tenth of it.
 tg_status infer_entries(Workspace& ws, uint32_t N, uint64_t space, const tg_region_req* rq, const uint64_t* req_ptr,
                         uint32_t shift, uint64_t nent_bound, hipStream_t st, uint64_t* pin, uint64_t* row, uint32_t** col,
                         bool alloc_col, uint64_t col_cap, uint64_t* E, bool* done) {
   *done = false;
   hipError_t e;
   const uint64_t nlists = 2 * (((space - 1) >> shift) + 1);
-  const size_t used0 = ws.used;
+  const size_t used0 = ws.used, owned0 = ws.owned.size();
+  auto give_up = [&] {  // everything taken here goes back, once the stream has finished with it
+    (void)hipGetLastError();
+    e = hipStreamSynchronize(st);
+    ws.rewind(used0, owned0);
+    return e == hipSuccess ? TG_OK
+                           : tg_set_error(TG_EDEVICE, "dependence inference (entries): %s", hipGetErrorString(e));
+  };
   // list sizes and the entry allocator are cleared together
   const size_t cnt_bytes = round256(nlists * 4), lptr_bytes = round256((nlists + 1) * 4);
   const size_t fixed = cnt_bytes + 256 + lptr_bytes + tg::kMaxTiles * 8 + 2 * round256((uint64_t)N * 4) + round256((uint64_t)N * 4);
   auto entry_bytes = [](uint64_t n) {
     return round256(n * sizeof(tg::Own)) + round256(n * sizeof(tg::Ent)) + 2 * round256(n * 4);
   };
-  auto fits = [&](uint64_t n) { return ws.spill || fixed + entry_bytes(n) + 8192 <= ws.cap - used0; };
+  auto fits = [&](uint64_t n) { return fixed + entry_bytes(n) + 8192 <= ws.cap - used0; };
   // (a fixed region that does not even hold the lists: the other pipeline)
-  if (!fits(0)) return TG_OK;
+  if (!ws.spill && !fits(0)) return TG_OK;
   uint8_t* fx = nullptr;
-  ICHK(ws.get(fixed, "lists", (void**)&fx), "lists");
+  e = ws.get(fixed, "lists", (void**)&fx);
+  if (e == hipErrorOutOfMemory) return give_up();
+  ICHK(e, "lists");
   tg::EntTables T;
   T.cnt = (uint32_t*)fx;
   unsigned long long* next = (unsigned long long*)(fx + cnt_bytes);
@@ -1168,7 +1192,7 @@ tg_status infer_entries(Workspace& ws, uint32_t N, uint64_t space, const tg_regi
   uint64_t nent = nent_bound;
   if (!fits(nent)) {
     // the bound allows two partly covered buckets per interval: ask for the
-    // number itself
+    // number itself before the entries are refused, or allocated
     if (pin) {
       ICHK(hipStreamSynchronize(st), "list scan");
       nent = __atomic_load_n(pin_n, __ATOMIC_ACQUIRE);
@@ -1177,13 +1201,12 @@ tg_status infer_entries(Workspace& ws, uint32_t N, uint64_t space, const tg_regi
       ICHK(read_back(&n32, lptr + nlists, 4, st), "entry count read-back");
       nent = n32;
     }
-    if (!fits(nent)) {
-      ws.used = used0;
-      return TG_OK;
-    }
+    if (!ws.spill && !fits(nent)) return give_up();
   }
   uint8_t* ex = nullptr;
-  ICHK(ws.get(entry_bytes(nent), "entries", (void**)&ex), "entries");
+  e = ws.get(entry_bytes(nent), "entries", (void**)&ex);
+  if (e == hipErrorOutOfMemory) return give_up();
+  ICHK(e, "entries");
   T.own = (tg::Own*)ex;
   T.ent = (tg::Ent*)(ex + round256(nent * sizeof(tg::Own)));
   T.utask = (uint32_t*)((uint8_t*)T.ent + round256(nent * sizeof(tg::Ent)));
@@ -1210,8 +1233,13 @@ tg_status infer_entries(Workspace& ws, uint32_t N, uint64_t space, const tg_regi
   } else {
     ICHK(read_back(E, row + N, 8, st), "edge count read-back");
   }
+  if (alloc_col && *E < 0xFFFFFFFFull) {
+    e = ws.get(*E * 4, "edges", (void**)col);
+    if (e == hipErrorOutOfMemory) return give_up();
+    ICHK(e, "edge array");
+  }
   *done = true;
-  const tg_status s = edge_buffer(ws, *E, col, alloc_col, col_cap);
+  const tg_status s = edge_count_ok(*E, alloc_col, col_cap);
   if (s != TG_OK) return s;
   if (*E) {
     hipLaunchKernelGGL(tg::k_rows_sorted<true>, dim3(rb), dim3(256), lds, st, T, N, wsh, rcnt, row, *col);

@@ -61,3 +61,32 @@ assert free_calls == [0, 0, 0], free_calls
 assert alloc_calls[0] > 0, "the shim saw nothing"
 print("done")
 """)
+
+
+@pytest.mark.parametrize("limit", [1 << 26, 20 << 20])
+def test_entries_beyond_the_device_memory(gpu, tmp_path, limit):
+    """800,000 writers of one element each, eight to an element: 38 MB of
+    entries by their number, 115 MB by the bound on it.  Where the device has
+    room for the former, or only for the smaller tables of the other pipeline
+    (no allocation above `limit` succeeds), the call still works."""
+    _run(tmp_path, f"""
+N, S = 800_000, 100_000
+k = np.arange(N, dtype=np.uint64)
+lo = k % np.uint64(S)
+ig = wl.ImplicitGraph(N=N, req_ptr=np.arange(N + 1, dtype=np.uint64), lo=lo, hi=lo + np.uint64(1),
+                      priv=np.full(N, tg.TG_RW, np.uint32), space=S, rounds=0)
+later = (N - 1 - np.arange(N)) // S
+def limited(*a):
+    shim.shim_limit({limit})
+    try:
+        return tg.tg_infer_dag(*a)
+    finally:
+        shim.shim_limit(1 << 60)
+row, col = infer_on_device(ig, col_cap=int(later.sum()), fn=limited)
+ref = np.zeros(N + 1, np.uint64)
+ref[1:] = np.cumsum(later)
+assert np.array_equal(row, ref)
+assert np.array_equal(col, np.repeat(np.arange(N), later) + S * (1 + np.arange(col.size) - np.repeat(ref[:-1].astype(np.int64), later)))
+if {limit} < 30_000_000: assert shim.shim_refused() > 0
+print("done")
+""")
