@@ -32,6 +32,7 @@
 // less memory runs instead (tables of interval indices, and rows sorted at the
 // end); see infer_core.
 #include "taskgraph.h"
+#include "tg_buckets.h"
 #include "tg_internal.h"
 
 #include <algorithm>
@@ -1089,22 +1090,6 @@ struct PinBlock {
   }
 };
 
-// Bucket width of the sorted entries: the length class that holds the median
-// element of all intervals (half of the length, rounded down to the class,
-// lies in shorter classes or this one), so most elements belong to intervals of one to three entries,
-// and short intervals beside long ones (halos) do not shrink the buckets.
-uint32_t entry_shift(const uint64_t* cls, uint64_t space, uint64_t max_buckets) {
-  long double total = 0, upto = 0;
-  for (int c = 0; c < 64; ++c) total += (long double)cls[c] * (long double)(1ull << c);
-  uint32_t shift = 0;
-  for (; shift < 63; ++shift) {
-    upto += (long double)cls[shift] * (long double)(1ull << shift);
-    if (2 * upto >= total) break;
-  }
-  while (shift < 63 && ((space - 1) >> shift) + 1 > max_buckets) shift++;
-  return shift;
-}
-
 #define ICHK(x, what)                                                                                   \
   do {                                                                                                  \
     e = (x);                                                                                            \
@@ -1298,13 +1283,13 @@ tg_status infer_steps(Workspace& ws, uint32_t N, uint64_t M, uint64_t space, con
     return TG_OK;
   }
   {
-    const uint32_t es = entry_shift(sum + tg::kSumClass, space, max_buckets / 2);
-    // an interval of length l touches at most (l >> shift) + 2 buckets, and one
-    // of a class that the total may have overflowed fewer than 2^(c + 1 - shift) + 2
-    long double bound = 2.0L * (long double)nonempty;
-    long double most = 0;
-    for (int c = 0; c < 64; ++c) most += (long double)sum[tg::kSumClass + c] * 2.0L * (long double)(1ull << c);
-    bound += (most < 1.8e19L ? (long double)sum[tg::kSumLen] : most) / (long double)(1ull << es);
+    // the total length, or a bound on it if it may have overflowed
+    long double length = 0;
+    for (int c = 0; c < 64; ++c) length += (long double)sum[tg::kSumClass + c] * 2.0L * (long double)(1ull << c);
+    if (length < 1.8e19L) length = (long double)sum[tg::kSumLen];
+    const uint32_t es = tg::entry_shift(sum + tg::kSumClass, nonempty, length, space, max_buckets / 2);
+    // an interval of length l touches at most (l >> shift) + 2 buckets
+    const long double bound = 2.0L * (long double)nonempty + length / (long double)(1ull << es);
     // 32-bit offsets inside a bucket, and 32-bit entry indices
     if (es <= 31 && bound < 4.0e9L) {
       bool done = false;

@@ -144,3 +144,22 @@ def test_capacity_below_the_edge_count(gpu):
                                 ctypes.c_void_p(d_col.data_ptr()), col.size - 1, ctypes.byref(e), None)
     assert st == tg.TG_ENOMEM and e.value == col.size
     assert (d_col == -7).all()
+
+
+@pytest.mark.parametrize("readers", [1, 2, 5])
+def test_whole_array_readers(gpu, readers):
+    """A halo program whose sweeps each end with tasks that read the whole array
+    (one of them also writes a word of its own): most declared elements are theirs,
+    and they have an entry in every bucket."""
+    P, S, sweeps = 48, 700, 12
+    rows = []
+    for k in range(sweeps):
+        for p in range(P):
+            row = [(p * S, p * S + S, 2)]
+            if p:
+                row.append((p * S - 5 - k, p * S, 1))
+            if p + 1 < P:
+                row.append((p * S + S, p * S + S + 17, 1))
+            rows.append(row)
+        rows += [[(0, P * S, 1)] + ([(P * S + k, P * S + k + 1, 2)] if r == 0 else []) for r in range(readers)]
+    _check(_program(rows, P * S + sweeps))
