@@ -110,7 +110,10 @@ typedef struct {
  *   schedule     : how tasks are partitioned over the workers' lists
  *                  (Algorithm 1, Compile); by default TG_SCHED_COLUMN for one
  *                  graph on wavefronts or workgroups whose `workers` is 0
- *                  too, else TG_SCHED_LEVEL.
+ *                  too, if the tasks of a level cost about the same or every
+ *                  task depends on the one before it in its column; else
+ *                  TG_SCHED_LEVEL (a column runs one after another, and
+ *                  independent tasks of very different costs would wait).
  *                  TG_SCHED_LEVEL sorts by
  *                  dependence level and deals round-robin; TG_SCHED_SPREAD
  *                  stretches every graph's levels over the same interval

@@ -12,6 +12,7 @@
 // topologically ordered, which is what makes the executor deadlock-free for
 // any ready-window length.
 #include "taskgraph.h"
+#include "tg_columns.h"
 #include "tg_internal.h"
 #include "tg_ledger.h"
 
@@ -510,6 +511,9 @@ struct tg_graph_s {
   DevBuf payload, data, digest, dblob;
   std::unique_ptr<Layout> solo;
   std::shared_ptr<PlanCache> plans;  // schedules of this graph alone, by (workers, schedule)
+  // the schedule the library chose for this graph alone and the mapping it was
+  // chosen for (0: not chosen since the tasks or edges last changed)
+  uint32_t own_schedule = 0, own_mapping = 0, own_wg_waves = 0;
   // execution state
   bool inflight = false;
   Layout* last_layout = nullptr;
@@ -627,12 +631,13 @@ struct HostLayout {
 // Estimated cost of a task, in lane-steps of one wavefront: a fixed latency
 // term (counter poll, payload hand-off, edge signals) plus the words it
 // touches times the mix rounds.  Only the schedule uses it; it is never 0.
+constexpr uint64_t kTaskLatency = 64;
+
 uint64_t task_cost(const tg_graph g, uint32_t v) {
-  constexpr uint64_t kLatency = 64;
   const uint64_t R = g->rounds[v];
   if (g->mode == TG_EXPLICIT) {
     const uint64_t npred = g->dpred_ptr[v + 1] - g->dpred_ptr[v];
-    return kLatency + (uint64_t)g->n / 64 * (R + npred + 1);
+    return kTaskLatency + (uint64_t)g->n / 64 * (R + npred + 1);
   }
   uint64_t ro = 0, rw = 0;
   for (uint64_t i = g->req_ptr[v]; i < g->req_ptr[v + 1]; ++i) {
@@ -640,7 +645,24 @@ uint64_t task_cost(const tg_graph g, uint32_t v) {
     const uint64_t len = q.hi > q.lo ? q.hi - q.lo : 0;
     (q.priv == TG_RW ? rw : ro) += len;
   }
-  return kLatency + (ro + rw * (R + 2)) / 64;
+  return kTaskLatency + (ro + rw * (R + 2)) / 64;
+}
+
+// Whether column order suits graph g on nw workers (tg_columns.h).  Here a task's
+// predecessors count in the groups of five that one round trip loads: level mates
+// that differ by a few predecessors take the same time.
+bool suits_columns(const tg_graph g, uint64_t nw) {
+  return tg::columns_hold(
+      g->level, nw,
+      [&](uint32_t v) {
+        if (g->mode != TG_EXPLICIT) return task_cost(g, v);
+        const uint64_t npred = g->dpred_ptr[v + 1] - g->dpred_ptr[v];
+        return kTaskLatency + (uint64_t)g->n / 64 * (g->rounds[v] + (npred + 4) / 5 * 5 + 1);
+      },
+      [&](uint32_t u, uint32_t v) {
+        const auto b = g->dpred.begin() + (ptrdiff_t)g->dpred_ptr[v], e = g->dpred.begin() + (ptrdiff_t)g->dpred_ptr[v + 1];
+        return std::find(b, e, u) != e;
+      });
 }
 
 // Dependence-level order: all tasks sorted by (level, graph, id) and dealt
@@ -2636,19 +2658,28 @@ static tg_status graph_execute(tg_graph g, const tg_exec_config* cfgp, void* str
     return fail(TG_EBUSY, "previous execution on another stream not waited for");
   const tg_exec_config* const given = cfgp ? cfgp : (g->has_tuned ? &g->tuned : nullptr);
   Config cfg = resolve(given);
-  // One graph whose schedule and workers are left to the library runs in column order:
-  // level order over all resident workers puts a task and its successor of the
-  // same lane on different ones as soon as the level's width does not divide
-  // their number, so every edge is a hand-off and thousands of workers poll.
-  // Measured (kernel, level / column, us): butterfly 300 x 100 265 / 164, random
-  // 1024 x 50 210 / 116, stencil 8 x 16 39 / 37, tree 1024 x 60 with 1024 rounds
-  // 3530 / 2880, halo 32 x 32 624 / 542, no dependences 1024 x 500 315 / 317.
-  // Gangs keep level order, the queue has no lists, and a batch of
-  // graphs of different widths and costs has no columns to keep.
-  if ((!given || (!given->schedule && !given->workers)) && cfg.dispatch == TG_DISPATCH_LISTS && cfg.mapping != TG_MAP_GANG)
-    cfg.schedule = TG_SCHED_COLUMN;
   tg_status s = check_config(cfg);
   if (s != TG_OK) return s;
+  // One graph whose schedule and workers are left to the library runs in column
+  // order if that suits it: level order over all resident workers puts a task and
+  // its successor of the same lane on different ones as soon as the level's width
+  // does not divide their number, so every edge is a hand-off and thousands of
+  // workers poll.  Measured (kernel, level / column, us): butterfly 300 x 100 265 /
+  // 164, random 1024 x 50 210 / 116, stencil 8 x 16 39 / 37, tree 1024 x 60 with 1024
+  // rounds 3530 / 2880, halo 32 x 32 624 / 542, no dependences 1024 x 500 315 / 317.
+  // Gangs keep level order, the queue has no lists, and a batch of
+  // graphs of different widths and costs has no columns to keep.
+  if ((!given || (!given->schedule && !given->workers)) && cfg.dispatch == TG_DISPATCH_LISTS &&
+      cfg.mapping != TG_MAP_GANG) {
+    if (!g->own_schedule || g->own_mapping != cfg.mapping || g->own_wg_waves != cfg.wg_waves) {
+      uint32_t nw = 0;
+      if ((s = resident_workers(cfg.mapping, cfg.wg_waves, &nw)) != TG_OK) return s;
+      g->own_schedule = suits_columns(g, nw) ? TG_SCHED_COLUMN : TG_SCHED_LEVEL;
+      g->own_mapping = cfg.mapping;
+      g->own_wg_waves = cfg.wg_waves;
+    }
+    cfg.schedule = g->own_schedule;
+  }
   if (!g->solo || !same_layout(g->solo->cfg, cfg)) {
     if (g->inflight && (s = graph_wait(g)) != TG_OK) return s;
     drop_solo(g);
@@ -3018,6 +3049,7 @@ tg_status tg_graph_reduce_edges(tg_graph g, uint64_t* removed) {
   // layouts and schedules were built on the full edge set
   drop_solo(g);
   g->plans.reset();
+  g->own_schedule = 0;
   g->has_tuned = false;
   if (removed) *removed = g->full_succ.size() - g->succ.size();
   return TG_OK;
@@ -3124,6 +3156,7 @@ tg_status tg_graph_set_rounds(tg_graph g, uint32_t uniform_rounds) {
   tg_status s = graph_wait(g);
   if (s != TG_OK) return s;
   std::fill(g->rounds.begin(), g->rounds.end(), uniform_rounds);
+  g->own_schedule = 0;
   if (g->finalized) {
     std::fill(g->blob.begin() + g->bo.rounds, g->blob.begin() + g->bo.rounds + g->N(), uniform_rounds);
     g->blob_gen++;
@@ -3357,7 +3390,10 @@ tg_status tg_batch_set_rounds(tg_batch b, uint32_t uniform_rounds) {
   if (!b) return fail(TG_EINVAL, "batch is NULL");
   tg_status s = tg_batch_wait(b);
   if (s != TG_OK) return s;
-  for (auto g : b->graphs) std::fill(g->rounds.begin(), g->rounds.end(), uniform_rounds);
+  for (auto g : b->graphs) {
+    std::fill(g->rounds.begin(), g->rounds.end(), uniform_rounds);
+    g->own_schedule = 0;
+  }
   Layout& L = *b->lay;
   for (auto& r : L.rec_host) r.rounds = uniform_rounds;
   if (!L.rec_host.empty())
