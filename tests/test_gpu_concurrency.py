@@ -57,6 +57,10 @@ def _run_pair(ga, gb, ca, cb):
         tg.tg_graph_execute(g.handle, c)
         tg.tg_graph_wait(g.handle)
     s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    for s in (s1, s2):  # a stream's first work makes its hardware queue: up to 4 ms, a launch here takes 0.5
+        with torch.cuda.stream(s):
+            torch.zeros(1, device="cuda")
+    torch.cuda.synchronize()
     tg.tg_graph_execute(ga.handle, ca, s1)
     tg.tg_graph_execute(gb.handle, cb, s2)
     tg.tg_graph_wait(ga.handle)
