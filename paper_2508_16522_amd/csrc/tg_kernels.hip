@@ -1118,10 +1118,11 @@ __device__ __forceinline__ uint32_t queue_next(const ExecParams& P, QueueState& 
     // worker waits for whichever task is pushed next, and in the serving
     // loop a late claim delays a request (median latency 9.7 ms with the
     // fixed back-off, 11.4 ms with the growing one, same box).  Four naps (0.2
-    // us) a poll: stencil 1024 x 500 1.76 ms, with one nap 1.80, with 16 1.83
+    // us) a poll for the first 64 (stencil 1024 x 500 1.76 ms, with one nap 1.80,
+    // with 16 1.83), then the configured number
     __builtin_amdgcn_s_setprio(kPrioPoll);
     for (uint32_t spins = 1;; ++spins) {
-      const uint32_t nap = spins < 64 ? 4u : max(P.idle_sleep, 4u);
+      const uint32_t nap = spins < 64 ? 4u : P.idle_sleep;
       for (uint32_t i = 0; i < nap; ++i) __builtin_amdgcn_s_sleep(2);
       v = uni(ld_coherent(slot));
       if (v != kQEmpty) break;

@@ -103,3 +103,10 @@ def test_pinned_pools_serve_every_device():
             body = src[src.index(pool + " {"):]
             calls = re.findall(r"hipHostMalloc\(([^;{]*)", body[:body.index("\n};")])
             assert calls and all("hipHostMallocPortable" in c for c in calls), pool
+
+
+def test_queue_workers_honour_idle_sleep():
+    # the configured back-off of a queue worker is the one it takes after its
+    # first 64 empty polls, whatever its value (lists: clamped, as documented)
+    body = dict(_functions(_source()))["queue_next"]
+    assert re.search(r"nap\s*=\s*spins\s*<\s*64\s*\?\s*\d+u\s*:\s*P\.idle_sleep\s*;", body)
