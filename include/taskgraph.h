@@ -43,6 +43,11 @@
  *     tg_set_allocator, else hipMalloc) and freed by the matching destroy.
  *   - Streams are hipStream_t passed as void*; NULL is the default stream.
  *   - A handle may be used by one thread at a time.
+ *   - Kernels of other streams may run beside a launch that leaves room for
+ *     them (fewer workers than are co-resident).  The launch's wavefronts run
+ *     above the default issue priority except while they poll: beside long mixes
+ *     (over about 5 us a task) on half of all wavefronts other kernels take up
+ *     to a fifth longer than beside as many wavefronts of equal priority.
  *   - All kernels bound every wait: a wait that sees no progress for the
  *     configured watchdog interval aborts the launch, and the following
  *     wait/read call returns TG_ETIMEOUT.

@@ -280,16 +280,24 @@ __device__ __forceinline__ typename VecT<VEC>::T gather5(const ExecParams& P, co
   return ((p0 + p1) + (p2 + p3)) + p4;
 }
 
-// Issue priority of a wavefront (0 lowest).  A SIMD's wavefronts share its issue
-// slots by priority, not evenly: first the scheduling, payload and signal
-// phases and short mixes, which are a few instructions between memory round
-// trips and which other tasks wait for; then the mixes, those of the longer
-// tasks first, since a chain of them is what a launch of uneven graphs ends with;
-// last the polls of waiting workers.  48 graphs of log-normal costs over 4096
+// Issue priority of a wavefront (0, the lowest, is the default).  A SIMD's
+// wavefronts share its issue slots by priority, not evenly.  At 3: the scheduling,
+// payload and signal phases, and mixes of fewer than 32 rounds, which are a few
+// instructions between memory round trips and which other tasks wait for.  Mixes
+// of 32 rounds or more by their length, long ones first, since a chain of them is
+// what a launch of uneven graphs ends with: 2, 1, and 0 for the short ones, which
+// then share with the polls of waiting workers (0 too, but mostly asleep).
+// 48 graphs of log-normal costs over 4096
 // workers: 31.9 ms, with equal priorities 38.4 (with all three mix classes at one
 // priority 35.3, with polls at the highest 34.2); the 1024-column halo program on
 // gangs 16.1 ms, 16.7 with equal ones.  The thresholds are rounds times words per lane:
 // about 5 us and 80 us of a SIMD's time.
+// Kernels of other streams on the same SIMD are at 0.  Beside 4096 workers (half of
+// them all) with tasks of 1024 rounds a function in 64-bit floats takes 12.4 times its
+// time alone, a matrix product 8.7 and an addition 2.8 times; beside the same
+// executor without priorities 11.0, 7.8 and 2.6 times; with 31 rounds or 2048 workers
+// there is no difference.  It is the mixes at 1 and 2 that cost this: with all of
+// them at 0 it is gone, and the 48 graphs' call takes 39.7 ms instead of 33.0.
 constexpr uint32_t kPrioPoll = 0, kPrioShort = 3;
 
 // Around the mix of a task of `len` words on S lanes (of one chunk, or of all: once

@@ -132,3 +132,36 @@ def test_graph_beside_server(gpu):
         else:
             ref = oracle.exec_explicit(x.N, x.n, x.pred_ptr, x.preds, x.rounds, seed=x.seed, want_payload=False)
         assert np.array_equal(tg.tg_graph_read_digests(h.handle), ref["digest"])
+
+
+@pytest.mark.parametrize("rounds", [31, 1024])
+def test_other_kernels_run_beside_an_executor(gpu, rounds):
+    """An executor whose workers fill half of every SIMD with mixes, at a raised
+    issue priority, does not shut out the kernels of another stream: they advance
+    while it runs.  (An addition of 2^22 floats takes some 10 us alone; the
+    executor runs for milliseconds.)"""
+    import torch
+    _, _, resident = tg.tg_exec_occupancy(tg.TG_MAP_WAVE, 4)
+    eg = wl.pattern_graph("stencil", resident // 2, 4096 // (rounds + 1) + 24, seed=7, n=256, rounds=rounds)
+    g = tg.graph_from_explicit(eg)
+    cfg = tg.make_config(mapping=1, workers=resident // 2, schedule=tg.TG_SCHED_COLUMN, watchdog_ms=3000)
+    x = torch.rand(1 << 22, device="cuda")
+    s1, s2 = torch.cuda.Stream(), torch.cuda.Stream()
+    tg.tg_graph_execute(g.handle, cfg, s1)
+    tg.tg_graph_wait(g.handle)
+    alone = tg.tg_graph_kernel_ms(g.handle)
+    with torch.cuda.stream(s2):
+        x + 1
+    torch.cuda.synchronize()
+    done, end = 0, torch.cuda.Event()
+    tg.tg_graph_execute(g.handle, cfg, s1)
+    end.record(s1)
+    with torch.cuda.stream(s2):
+        while not end.query():
+            x + 1
+            e = torch.cuda.Event()
+            e.record()
+            e.synchronize()
+            done += 1
+    tg.tg_graph_wait(g.handle)
+    assert done >= 2 * alone, f"{done} additions during an execution of {alone:.1f} ms alone"
