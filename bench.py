@@ -355,7 +355,7 @@ def main():
     else:
         probes = {
             "mix_word_rounds_per_s": tg.tg_probe(tg.TG_PROBE_MIX_RATE),
-            "alu_peak_word_rounds_per_s": bw.ALU_PEAK_WORD_ROUNDS,
+            "alu_nominal_word_rounds_per_s": bw.ALU_NOMINAL_WORD_ROUNDS,
             "copy_bytes_per_s": tg.tg_probe(tg.TG_PROBE_COPY_BW),
             "atomics_distinct_per_s": tg.tg_probe(tg.TG_PROBE_ATOMIC_DISTINCT),
             "atomics_contended_per_s": tg.tg_probe(tg.TG_PROBE_ATOMIC_CONTENDED),
@@ -505,7 +505,7 @@ def main():
             gran_us = ms * 1e3 * slots / tasks_per_step
             rows.append({"rounds": R, "ms": ms, "word_rounds_per_s": U / (ms * 1e-3) if R else 0.0,
                          "efficiency": eff, "granularity_us": gran_us,
-                         "frac_of_alu_peak": (U / (ms * 1e-3)) / bw.ALU_PEAK_WORD_ROUNDS if R else 0.0,
+                         "frac_of_alu_nominal": (U / (ms * 1e-3)) / bw.ALU_NOMINAL_WORD_ROUNDS if R else 0.0,
                          "launch": {k: rcfg[k] for k in ("mapping", "workers", "wg_waves", "notify", "schedule")}})
             log(f"sweep R={R}: {ms:.3f} ms eff {eff:.3f} gran {gran_us:.2f} us")
         tg.tg_batch_set_rounds(batch, 0)

@@ -23,12 +23,13 @@ from paper_2508_16522_amd import workloads as wl
 
 METRIC = "tasks/sec + per-task overhead (ns) + min effective task granularity, 1 GPU"
 ROOT = os.path.dirname(os.path.abspath(__file__))
-# integer-VALU peak of the task body: 256 CUs x 2.4 GHz x 64 lanes per clock
-# (four SIMDs of 16; every instruction of the mix, the 32-bit multiply and the
-# 64-bit shifts included, was measured at four cycles per wavefront), and six
+# Nominal integer rate of the task body, for orientation: one 64-lane
+# instruction per CU and cycle (four SIMDs of 16 lanes) at 2.4 GHz on 256 CUs, six
 # instructions per word-round (three shifts, two of them shared by two words,
-# three xors, one of which also adds, and a multiply).
-ALU_PEAK_WORD_ROUNDS = 256 * 2.4e9 * 64 / 6
+# three xors, one of which also adds, and a multiply).  No bound: with eight
+# wavefronts a SIMD the mix alone issues 1.02 instructions per CU and cycle at
+# 2.39 GHz.  Efficiencies are taken against the best measured rate.
+ALU_NOMINAL_WORD_ROUNDS = 256 * 2.4e9 * 64 / 6
 
 
 def log(msg):
@@ -195,7 +196,7 @@ def run_implicit(args, stream, probes=None):
         "compile_ms": tm["compile_ms"], "host_build_s": host_s, "launch": cfg,
         "exec_ms": ms, "tasks_per_s": ig.N / (ms * 1e-3), "word_rounds_per_s": word_rounds / (ms * 1e-3),
         "frac_of_measured_mix_rate": word_rounds / (ms * 1e-3) / pi if pi else None,
-        "frac_of_alu_peak": word_rounds / (ms * 1e-3) / ALU_PEAK_WORD_ROUNDS,
+        "frac_of_alu_nominal": word_rounds / (ms * 1e-3) / ALU_NOMINAL_WORD_ROUNDS,
         "parity": {"ok": ok, "against": "oracle program order, stored by tests/golden/make_halo_program_r64.py: "
                                         "checksum, SHA-256 of all 65536 digests and of the 2^24-element array"},
         "reduced": {"edges": E - removed, "reduce_ms": reduce_ms, "launch": rcfg, "exec_ms": rms, "parity": rok},
@@ -302,7 +303,7 @@ def run_batch(args, stream, probes=None):
         "word_rounds_per_s": U / (ms * 1e-3),
         "frac_of_measured_mix_rate": (U / (ms * 1e-3) / probes["mix_word_rounds_per_s"]
                                       if probes and probes.get("mix_word_rounds_per_s") else None),
-        "frac_of_alu_peak": U / (ms * 1e-3) / ALU_PEAK_WORD_ROUNDS,
+        "frac_of_alu_nominal": U / (ms * 1e-3) / ALU_NOMINAL_WORD_ROUNDS,
         "retention": retention, "payload_bytes": payload_bytes, "payload_bytes_keep_all": payload_bytes_all,
         "host_build_s": build_s, "layout_s": layout_s, "layout_ms": btimes,
     }

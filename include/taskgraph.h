@@ -111,7 +111,8 @@ typedef struct {
  *                  (1..64, default 2), after its first 64 empty polls; with
  *                  the lists it is at least 16 units there and doubles after
  *                  every further 64 empty polls, up to 32 times this value (at
- *                  most 256 units).
+ *                  most 256 units).  (Before that: lists 1 to 16 units, growing;
+ *                  queue 4.)
  *   schedule     : how tasks are partitioned over the workers' lists
  *                  (Algorithm 1, Compile); by default TG_SCHED_COLUMN for one
  *                  graph on wavefronts or workgroups whose `workers` is 0
@@ -384,7 +385,7 @@ tg_status tg_last_user_dag(uint32_t n, const uint64_t* req_ptr, const tg_region_
  *   req_ptr     : device, ntasks + 1 u64; task k's requirements are
  *                 reqs[req_ptr[k] .. req_ptr[k+1]); req_ptr[0] = 0,
  *                 non-decreasing, req_ptr[ntasks] = nreqs.
- *   reqs        : device, nreqs tg_region_req records (32 bytes each);
+ *   reqs        : device, nreqs tg_region_req records (24 bytes each);
  *                 intervals lie inside [0, index_space); a task's read-write
  *                 interval overlaps none of its own other intervals.
  *   row_ptr     : device, ntasks + 1 u64, written: the out-edge CSR.
@@ -398,7 +399,9 @@ tg_status tg_last_user_dag(uint32_t n, const uint64_t* req_ptr, const tg_region_
  * The caller owns every array.  Scratch device memory (interval lists,
  * counts, scan partials) comes from a 32 MiB array of device memory in the
  * library's code object if no other call has it, else (and where it does not
- * fit) from hipMalloc, freed before the call returns.  TG_EINVAL for a bad requirement list (the
+ * fit) from hipMalloc, freed before the call returns; where that finds no room
+ * for the entries (48 bytes each), smaller and slower tables are used.
+ * TG_EINVAL for a bad requirement list (the
  * message names the fault), TG_EDEVICE for a HIP error. */
 tg_status tg_infer_dag(uint32_t ntasks, const uint64_t* req_ptr, const tg_region_req* reqs, uint64_t nreqs,
                        uint64_t index_space, uint64_t* row_ptr, uint32_t* col, uint64_t col_cap, uint64_t* num_edges,
@@ -409,12 +412,16 @@ tg_status tg_infer_dag(uint32_t ntasks, const uint64_t* req_ptr, const tg_region
  * 16 MiB array of device memory in the library's code object, one copy per
  * device, held until the process ends; the call fails with TG_ENOMEM (the
  * message names the array that did not fit) when the requirement list needs
- * more.  The interval table takes 32 bytes per requirement and the row counts
- * 4 bytes per task, so about 400,000 requirements fit (the 65,536-task halo
- * program with 196,480 requirements takes about 9 MiB).  Every call on a
+ * more.  Sorted entries take 48 bytes for every bucket an interval overlaps
+ * (mostly one to three) and 12 bytes per task (the 65,536-task halo program
+ * with 196,480 requirements: 10 MB in all); where they do not fit, slower
+ * tables of 32 bytes per requirement, 4 per entry and 4 per task do, so about
+ * 400,000 requirements fit.  Every call on a
  * device shares that device's array and leaves its contents behind; each call
  * clears what it reads before writing it.  Calls from this process on one
  * device are serialised by a lock; calls from two processes use two copies.
+ * Small results come back through pinned words if an allocating inference of
+ * this process has made some, else by copies (about 10 us each).
  * Outputs are unspecified after an error other than TG_ENOMEM for col_cap. */
 tg_status tg_infer_dag_noalloc(uint32_t ntasks, const uint64_t* req_ptr, const tg_region_req* reqs, uint64_t nreqs,
                                uint64_t index_space, uint64_t* row_ptr, uint32_t* col, uint64_t col_cap,

@@ -1,7 +1,7 @@
 // Roofline probes: the denominators of the executor's roofline fractions,
 // measured on the device the library runs on.
 //   mix rate      : word-rounds/s of a dependency-free kernel running the
-//                   task body's mix (the plain integer-VALU peak): the
+//                   task body's mix (the best rate it is known to reach): the
 //                   better of a one-vector-per-lane grid and a persistent
 //                   two-vector-per-lane grid;
 //   copy bandwidth: HBM bytes/s (read + write) of a streaming copy;

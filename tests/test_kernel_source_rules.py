@@ -6,7 +6,7 @@ and the implicit array -- is read and written only through the device-coherent
 helpers (agent-scope atomics `ld_coherent` / `st_coherent` / `__hip_atomic_*`,
 `sc1` buffer loads and stores `buf_load` / `buf_store`); a plain access is
 allowed only in the kernels that run before the executor in stream order (the
-reset, queue clear and queue seed).  Diagnostics the host reads after a launch
+reset and the queue clear).  Diagnostics the host reads after a launch
 are exempt.  The helpers themselves must keep their scope, and a task's edge
 signals must follow its store drain."""
 import os
@@ -17,7 +17,7 @@ SRC = os.path.join(ROOT, "paper_2508_16522_amd", "csrc", "tg_kernels.hip")
 
 # plain accesses are fine here: these kernels run before the executor on the
 # same stream, so the kernel boundary orders them
-BEFORE_EXECUTOR = {"k_reset", "k_queue_clear", "k_queue_seed"}
+BEFORE_EXECUTOR = {"k_reset", "k_queue_clear"}
 SHARED = re.compile(r"P\.(cnt|q|qctl|bell|gdone)\s*\[|P\.ctrl\s*->|\.digest\s*\[|\.out\s*\[|\bA\s*\[|\ba\s*\[")
 COHERENT = ("ld_coherent(", "st_coherent(", "__hip_atomic_", "buf_load", "buf_store", "__builtin_amdgcn_raw_buffer_")
 
